@@ -377,8 +377,8 @@ int mppi_batch_graph_launch(mppi_batch_t b, void* stream);
 /* Advances every problem's measured state (io->q, io->qd, written in place;
  * the io struct's const is cast away for these two) by dt seconds of the
  * FP64 zero-order-hold plant of mppi_plant_step_async, holding the first
- * row of the problem's io->U_new (clamped to the torque limits).  One
- * workgroup per problem. */
+ * row of the problem's io->U_new (clamped to the torque limits).  Eight
+ * lanes per problem. */
 int mppi_batch_plant_step_async(mppi_batch_t b, const mppi_batch_io* io, double dt, int substeps, void* stream);
 
 /* ---- warm start for a solver period that differs from dt ---- */

@@ -292,9 +292,11 @@ template <typename R> MPPI_HD void group_factor(const R* X, GroupFactor<R>& f, R
 // dynamics chain; otherwise group_cost forms it from the handoff.  The
 // update kernel chooses FDYN when the cost part also carries the collision
 // pairs, so that neither part runs both.
+// wrench: when given, a further world wrench [force; moment] at the EE
+// point, acting on the EE lane at this step's state (J(q)^T W on the joints).
 template <typename R, bool FORCE, class G, bool FDYN = false, bool HANDOFF = false>
 MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, const R* grav, int ext, R q, R qd,
-                         R tau, R v, R* X, GroupFactor<R>* fac, R* p, R* Q)
+                         R tau, R v, R* X, GroupFactor<R>* fac, R* p, R* Q, const R* wrench = nullptr)
 {
     const int j = g.j;
     const bool ee = j == kGroup - 1;
@@ -391,6 +393,10 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
         if (ee) {
             f[3] -= wn[0] * mag; f[4] -= wn[1] * mag; f[5] -= wn[2] * mag;
         }
+    }
+    if (wrench && ee) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) { f[a] -= wrench[3 + a]; f[3 + a] -= wrench[a]; }
     }
 
     // ---- subtree sums: bias forces and composite inertias

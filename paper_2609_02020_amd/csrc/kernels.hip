@@ -20,7 +20,7 @@
 //                   warm start.
 //   prep_model_kernel: parallel-axis shift of the link inertias (create).
 //   plant_kernel, batch_plant_kernel: FP64 zero-order-hold plant for the
-//                   closed loop (one problem, or one workgroup per problem).
+//                   closed loop (eight lanes per problem).
 //   select_kernel, batch_select_kernel: noise-free costs of the warm start
 //                   and a proposed nominal sequence; keeps the cheaper.
 #include <hip/hip_runtime.h>
@@ -341,64 +341,66 @@ constexpr int kGroupTile = kGroupSamples + 1;   // row stride of the workgroup's
 __device__ __forceinline__ int group_joint(int lane) { return (lane >> 1) & 7; }
 __device__ __forceinline__ int group_sample(int lane) { return (lane & 1) | ((lane >> 4) << 1); }
 
-struct DevGroup {
+// One DPP move of x (old: what lanes without a source keep; BC: they read 0
+// instead); a double moves as its two halves.
+template <int CTRL, int RM, int BM, bool BC> __device__ __forceinline__ float dpp(float old, float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), CTRL, RM, BM, BC));
+}
+template <int CTRL, int RM, int BM, bool BC> __device__ __forceinline__ double dpp(double old, double x)
+{
+    return __hiloint2double(
+        __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(x), CTRL, RM, BM, BC),
+        __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(x), CTRL, RM, BM, BC));
+}
+
+template <typename R> struct DevGroup {
     int j;
-    float* shm;
+    R* shm;
     // joint j - D's value (0 for j < D)
-    template <int D> __device__ float shr(float x) const
-    {
-        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x110 + 2 * D, 0xF, 0xF, true));
-    }
+    template <int D> __device__ R shr(R x) const { return dpp<0x110 + 2 * D, 0xF, 0xF, true>(R(0), x); }
     // joint j - D's value (1 for j < D: the shift leaves the old value)
-    template <int D> __device__ float shr_one(float x) const
-    {
-        return __int_as_float(
-            __builtin_amdgcn_update_dpp(__float_as_int(1.0f), __float_as_int(x), 0x110 + 2 * D, 0xF, 0xF, false));
-    }
-    // x plus joint j - D's value (j < D: plus 0), one DPP add
-    template <int D> __device__ float add_shr(float x) const { return x + shr<D>(x); }
-    // x plus joint j + D's value (j + D > 7: plus 0), one DPP add
-    template <int D> __device__ float add_shl(float x) const
-    {
-        return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x100 + 2 * D, 0xF, 0xF, true));
-    }
+    template <int D> __device__ R shr_one(R x) const { return dpp<0x110 + 2 * D, 0xF, 0xF, false>(R(1), x); }
+    // x plus joint j - D's value (j < D: plus 0), in FP32 one DPP add
+    template <int D> __device__ R add_shr(R x) const { return x + shr<D>(x); }
+    // x plus joint j + D's value (j + D > 7: plus 0), in FP32 one DPP add
+    template <int D> __device__ R add_shl(R x) const { return x + dpp<0x100 + 2 * D, 0xF, 0xF, true>(R(0), x); }
     // joint K's value: within every bank of four lanes (joints 2 m, 2 m + 1
     // of both samples) the lanes of joint 2 m + (K & 1) spread over the
     // bank, then bank K / 2 is copied into the other three by two masked
     // row shifts
-    template <int K> __device__ float bcast(float x) const
+    template <int K> __device__ R bcast(R x) const
     {
         constexpr int h = 2 * (K & 1);
-        int t = __builtin_amdgcn_mov_dpp(__float_as_int(x), h | ((h + 1) << 2) | (h << 4) | ((h + 1) << 6), 0xF, 0xF,
-                                         true);
+        R t = dpp<h | ((h + 1) << 2) | (h << 4) | ((h + 1) << 6), 0xF, 0xF, true>(R(0), x);
         constexpr int b = K >> 1;
-        if (b == 0) {
-            t = __builtin_amdgcn_update_dpp(t, t, 0x114, 0xF, 0x2, false);   // bank 1 <- 0
-            t = __builtin_amdgcn_update_dpp(t, t, 0x118, 0xF, 0xC, false);   // banks 2, 3 <- 0, 1
-        } else if (b == 1) {
-            t = __builtin_amdgcn_update_dpp(t, t, 0x104, 0xF, 0x1, false);   // bank 0 <- 1
-            t = __builtin_amdgcn_update_dpp(t, t, 0x118, 0xF, 0xC, false);   // banks 2, 3 <- 0, 1
-        } else if (b == 2) {
-            t = __builtin_amdgcn_update_dpp(t, t, 0x114, 0xF, 0x8, false);   // bank 3 <- 2
-            t = __builtin_amdgcn_update_dpp(t, t, 0x108, 0xF, 0x3, false);   // banks 0, 1 <- 2, 3
+        if constexpr (b == 0) {
+            t = dpp<0x114, 0xF, 0x2, false>(t, t);   // bank 1 <- 0
+            t = dpp<0x118, 0xF, 0xC, false>(t, t);   // banks 2, 3 <- 0, 1
+        } else if constexpr (b == 1) {
+            t = dpp<0x104, 0xF, 0x1, false>(t, t);   // bank 0 <- 1
+            t = dpp<0x118, 0xF, 0xC, false>(t, t);   // banks 2, 3 <- 0, 1
+        } else if constexpr (b == 2) {
+            t = dpp<0x114, 0xF, 0x8, false>(t, t);   // bank 3 <- 2
+            t = dpp<0x108, 0xF, 0x3, false>(t, t);   // banks 0, 1 <- 2, 3
         } else {
-            t = __builtin_amdgcn_update_dpp(t, t, 0x104, 0xF, 0x4, false);   // bank 2 <- 3
-            t = __builtin_amdgcn_update_dpp(t, t, 0x108, 0xF, 0x3, false);   // banks 0, 1 <- 2, 3
+            t = dpp<0x104, 0xF, 0x4, false>(t, t);   // bank 2 <- 3
+            t = dpp<0x108, 0xF, 0x3, false>(t, t);   // banks 0, 1 <- 2, 3
         }
-        return __int_as_float(t);
+        return t;
     }
     // over the group: joints j ^ 1, ^ 2, ^ 4 are lanes ^ 2, ^ 4, ^ 8, each
     // reached by DPP within the row (a quad permutation, then pairs of
     // bank-masked row shifts by 4 and by 8)
-    __device__ float sum(float x) const
+    __device__ R sum(R x) const
     {
-        x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, true));   // [2,3,0,1]
-        int t = __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x104, 0xF, 0x5, false);   // banks 0, 2 <- +4
-        t = __builtin_amdgcn_update_dpp(t, __float_as_int(x), 0x114, 0xF, 0xA, false);       // banks 1, 3 <- -4
-        x += __int_as_float(t);
-        t = __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x108, 0xF, 0x3, false);       // banks 0, 1 <- +8
-        t = __builtin_amdgcn_update_dpp(t, __float_as_int(x), 0x118, 0xF, 0xC, false);       // banks 2, 3 <- -8
-        return x + __int_as_float(t);
+        x += dpp<0x4E, 0xF, 0xF, true>(R(0), x);   // [2,3,0,1]
+        R t = dpp<0x104, 0xF, 0x5, false>(R(0), x);   // banks 0, 2 <- +4
+        t = dpp<0x114, 0xF, 0xA, false>(t, x);        // banks 1, 3 <- -4
+        x += t;
+        t = dpp<0x108, 0xF, 0x3, false>(R(0), x);     // banks 0, 1 <- +8
+        t = dpp<0x118, 0xF, 0xC, false>(t, x);        // banks 2, 3 <- -8
+        return x + t;
     }
     __device__ void sync() const { wave_sync(); }
 };
@@ -467,31 +469,31 @@ __global__ __launch_bounds__(kGroupThreads) void update_group_kernel(
         if (dyn) {
             if (s < T) {
                 float* X = gx[s & 1][grp];
-                const DevGroup g{j, X};
+                const DevGroup<float> g{j, X};
                 const float v = (Us[s * NJ + jc] + nb[s & 1][grp][j]) * L.live;
                 float p[3], Q[9];
-                const float qdd = group_dynamics<float, FORCE, DevGroup, COLL, true>(g, L, C, grav, ext, q, qd, v + te, v, X,
+                const float qdd = group_dynamics<float, FORCE, DevGroup<float>, COLL, true>(g, L, C, grav, ext, q, qd, v + te, v, X,
                                                                                nullptr, p, Q);
                 qd += qdd * dt;
                 q += qd * dt;
             } else {
                 // phi(x_T) (lane 7: q = qd = 0), while the cost wave
                 // evaluates step T - 1
-                const DevGroup g{j, gx[s & 1][grp]};
+                const DevGroup<float> g{j, gx[s & 1][grp]};
                 tS[grp][j] = group_terminal(g, L, C, tg, q, qd);
             }
         } else {
             if (s + 1 < T) draw(s + 1);
             if (s >= 1) {
                 float* X = gx[(s - 1) & 1][grp];
-                const DevGroup g{j, X};
+                const DevGroup<float> g{j, X};
                 const float* h = X + kGxH + j * 12;
                 float pe[3], Re[9];
 #pragma unroll
                 for (int a = 0; a < 3; ++a) pe[a] = h[a];
 #pragma unroll
                 for (int a = 0; a < 9; ++a) Re[a] = h[3 + a];
-                Sl += group_cost<float, FORCE, COLL, DevGroup, COLL, true>(g, L, C, tg, grav, X, nullptr, h[0], h[1], h[2], pe,
+                Sl += group_cost<float, FORCE, COLL, DevGroup<float>, COLL, true>(g, L, C, tg, grav, X, nullptr, h[0], h[1], h[2], pe,
                                                                      Re);
             }
         }
@@ -499,7 +501,7 @@ __global__ __launch_bounds__(kGroupThreads) void update_group_kernel(
     }
     // the terminal cost from the dynamics wave (ordered by the last barrier)
     if (!dyn) {
-        const DevGroup g{j, gx[T & 1][grp]};
+        const DevGroup<float> g{j, gx[T & 1][grp]};
         Sl += tS[grp][j];
         const float tot = g.sum(Sl);
         float sv = INFINITY;
@@ -928,17 +930,17 @@ __global__ __launch_bounds__(64 * kBatchGroupWaves) void batch_group_kernel(
         }
         // every group rolls out (samples past K too, storing nothing), so
         // the DPP moves always see a converged wave
-        const DevGroup g{j, gx[grp]};
+        const DevGroup<float> g{j, gx[grp]};
         float S;
         if (COLL && Pb.coll)
-            S = Pb.force ? group_rollout<float, true, DevGroup, float, true>(g, L, C, tg, grav, q0, qd0, te, Us, T,
+            S = Pb.force ? group_rollout<float, true, DevGroup<float>, float, true>(g, L, C, tg, grav, q0, qd0, te, Us, T,
                                                                               seed, tick, (uint32_t)k, nullptr, 0, nullptr, 0, true)
-                         : group_rollout<float, false, DevGroup, float, true>(g, L, C, tg, grav, q0, qd0, te, Us, T,
+                         : group_rollout<float, false, DevGroup<float>, float, true>(g, L, C, tg, grav, q0, qd0, te, Us, T,
                                                                                seed, tick, (uint32_t)k, nullptr, 0, nullptr, 0, true);
         else
-            S = Pb.force ? group_rollout<float, true, DevGroup, float>(g, L, C, tg, grav, q0, qd0, te, Us, T, seed,
+            S = Pb.force ? group_rollout<float, true, DevGroup<float>, float>(g, L, C, tg, grav, q0, qd0, te, Us, T, seed,
                                                                        tick, (uint32_t)k, nullptr, 0, nullptr, 0, true)
-                         : group_rollout<float, false, DevGroup, float>(g, L, C, tg, grav, q0, qd0, te, Us, T, seed,
+                         : group_rollout<float, false, DevGroup<float>, float>(g, L, C, tg, grav, q0, qd0, te, Us, T, seed,
                                                                         tick, (uint32_t)k, nullptr, 0, nullptr, 0, true);
         float sv = INFINITY;
         if (k < K) {
@@ -1075,48 +1077,62 @@ __global__ __launch_bounds__(kWeightsBlock) void weights_kernel(
     if (status && blockIdx.x == 0 && tid == 0) *status = MPPI_OK;
 }
 
-// zero-order hold of u (clamped to the torque limits) over dt in
+// Zero-order hold of u (clamped to the torque limits) over dt in
 // `substeps` semi-implicit Euler steps of the FP64 dynamics, with the cost's
 // external-wrench model and, when `wrench` is non-null, a further world
 // wrench [force; moment] at the EE point (a disturbance the controller does
-// not model), J(q)^T wrench at the state of every substep
-__device__ void plant_advance(const ModelM<double>& M, const CostM<double>& C, double* q, double* qd,
-                              const double* u, double dt, int substeps, const double* wrench)
+// not model), J(q)^T wrench at the state of every substep.  The plant is one
+// dependent chain of substeps and nothing else, so its time is the length of
+// that chain: eight lanes per problem (group.hpp, one joint each) run it, and
+// a wave takes eight problems.  Ten substeps of one arm take 25.4 us, where
+// one lane per problem (the articulated-body step, 4 KB of scratch) took
+// 453 us; of 50 arms 28.4 us (437 us).
+struct PlantProblem {
+    const ModelM<double>* M;
+    const CostM<double>* C;
+    const double* u;
+    double *q, *qd;
+};
+__device__ __forceinline__ void plant_advance(const PlantProblem& P, int lane, bool write, double dt, int substeps,
+                                              const double* wrench, double* X)
 {
-    double tau[NJ], qq[NJ], qv[NJ], W[6];
-    for (int j = 0; j < NJ; ++j) {
-        double lim = M.L[j].taumax;
-        tau[j] = fmin(fmax(u[j], -lim), lim);
-        qq[j] = q[j];
-        qv[j] = qd[j];
-    }
-    for (int c = 0; c < 6; ++c) W[c] = wrench ? wrench[c] : 0.0;
-    const int ext = C.ext_mode == EXTW_WALL ? EXTW_WALL : (C.ext_mode == EXTW_CONST ? EXTW_CONST : EXTW_NONE);
+    const int j = group_joint(lane), jc = j < NJ ? j : NJ - 1;
+    const ModelM<double>& M = *P.M;
+    const CostM<double>& C = *P.C;
+    GroupLink<double> L;
+    group_link(M, C, j, L);
+    const double grav[3] = {M.g[0], M.g[1], M.g[2]};
+    const int ext = C.ext_mode == EXTW_WALL ? EXTW_WALL : EXTW_NONE;
+    const double k = C.ext_mode == EXTW_CONST ? 1.0 : 0.0;
+    double W[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) W[c] = k * C.F_ext[c] + (wrench ? wrench[c] : 0.0);
     const double h = dt / substeps;
+    const bool live = j < NJ;   // lane 7: the EE frame, no joint
+    const double tau = live ? fmin(fmax(P.u[jc], -L.taumax), L.taumax) : 0.0;
+    double q = live ? P.q[jc] : 0.0, qd = live ? P.qd[jc] : 0.0;
+    const DevGroup<double> g{j, X};
     for (int s = 0; s < substeps; ++s) {
-        double ts[NJ];
-        if (wrench) {
-            ee_wrench_torque(M, qq, W, ts);
-            for (int j = 0; j < NJ; ++j) ts[j] += tau[j];
-        } else {
-            for (int j = 0; j < NJ; ++j) ts[j] = tau[j];
-        }
-        StepOut<double> o;
-        dyn_step<double, false>(M, C, ext, qq, qv, ts, ts, o);
-        for (int j = 0; j < NJ; ++j) {
-            qv[j] += o.qdd[j] * h;
-            qq[j] += qv[j] * h;
-        }
+        double p[3], Q[9];
+        const double qdd = group_dynamics<double, false, DevGroup<double>>(g, L, C, grav, ext, q, qd, tau, tau, X,
+                                                                           nullptr, p, Q, W);
+        qd += qdd * h;
+        q += qd * h;
     }
-    for (int j = 0; j < NJ; ++j) { q[j] = qq[j]; qd[j] = qv[j]; }
+    if (write && live) {
+        P.q[j] = q;
+        P.qd[j] = qd;
+    }
 }
 
-__global__ void plant_kernel(const ModelM<double>* __restrict__ Mp, const CostM<double>* __restrict__ Cp,
-                             double* q, double* qd, const double* __restrict__ u, double dt, int substeps,
-                             const double* __restrict__ wrench)
+__global__ __launch_bounds__(64) void plant_kernel(const ModelM<double>* __restrict__ Mp,
+                                                   const CostM<double>* __restrict__ Cp, double* q, double* qd,
+                                                   const double* u, double dt, int substeps, const double* wrench)
 {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    plant_advance(*Mp, *Cp, q, qd, u, dt, substeps, wrench);
+    __shared__ double X[8][kGxCount];
+    const int grp = group_sample(threadIdx.x);
+    // every group steps the one problem (converged waves), the first writes it
+    plant_advance(PlantProblem{Mp, Cp, u, q, qd}, threadIdx.x, grp == 0, dt, substeps, wrench, X[grp]);
 }
 
 // EE pose of n states (FP64): position and the unit quaternion (w, x, y, z)
@@ -1155,14 +1171,15 @@ __global__ void ee_pose_kernel(const ModelM<double>* __restrict__ Mp, const doub
     o[3] = sg * w; o[4] = sg * x; o[5] = sg * y; o[6] = sg * z;
 }
 
-// one workgroup per problem of a batch: the first row of its U_new
-__global__ void batch_plant_kernel(const BatchProblem* __restrict__ probs, int n, double* q, double* qd,
-                                   const double* __restrict__ U_new, double dt, int substeps)
+// the problems of a batch, eight to a wave: the first row of their U_new
+__global__ __launch_bounds__(64) void batch_plant_kernel(const BatchProblem* __restrict__ probs, int n, double* q,
+                                                         double* qd, const double* U_new, double dt, int substeps)
 {
-    const int p = blockIdx.x;
-    if (p >= n || threadIdx.x != 0) return;
+    __shared__ double X[8][kGxCount];
+    const int grp = group_sample(threadIdx.x), i = blockIdx.x * 8 + grp, p = min(i, n - 1);
     const BatchProblem& Pb = probs[p];
-    plant_advance(*Pb.model64, *Pb.cost64, q + p * NJ, qd + p * NJ, U_new + Pb.u_off, dt, substeps, nullptr);
+    plant_advance(PlantProblem{Pb.model64, Pb.cost64, U_new + Pb.u_off, q + p * NJ, qd + p * NJ}, threadIdx.x, i < n,
+                  dt, substeps, nullptr, X[grp]);
 }
 
 // Warm start after s horizon steps of elapsed time (solver period != dt):
@@ -1468,7 +1485,7 @@ hipError_t launch_ee_pose(const ModelM<double>* M, const double* q, int n, doubl
 hipError_t launch_batch_plant(const void* probs, int n, double* q, double* qd, const double* U_new, double dt,
                               int substeps, hipStream_t s)
 {
-    hipLaunchKernelGGL(batch_plant_kernel, dim3(n), dim3(64), 0, s, (const BatchProblem*)probs, n, q, qd, U_new,
+    hipLaunchKernelGGL(batch_plant_kernel, dim3((n + 7) / 8), dim3(64), 0, s, (const BatchProblem*)probs, n, q, qd, U_new,
                        dt, substeps);
     return hipGetLastError();
 }

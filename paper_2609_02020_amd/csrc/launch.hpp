@@ -87,8 +87,9 @@ hipError_t launch_batch_plant(const void* probs, int n, double* q, double* qd, c
 hipError_t launch_warm_start(const double* U, double* out, int T, double shift, hipStream_t s);
 hipError_t launch_batch_warm_start(const void* probs, int n, const double* U, double* out, double shift,
                                    hipStream_t s);
-hipError_t launch_batch_select(const void* probs, int n, const double* q, const double* qd, const double* target,
-                               double* U_nom, const double* U_cand, double* costs, hipStream_t s);
+hipError_t launch_batch_select(const void* probs, const void* models, int n, const double* q, const double* qd,
+                               const double* target, double* U_nom, const double* U_cand, double* costs,
+                               hipStream_t s);
 // model/cost: ModelM<R>/CostM<R> of the rollout precision
 hipError_t launch_select(int precision, bool force, bool coll, const void* model, const void* cost,
                          const double* q0, const double* qd0, const double* target, double* U_nom,

@@ -983,7 +983,7 @@ int mppi_batch_select_nominal_async(mppi_batch_t b, const mppi_batch_io* io, con
                                     double* costs, void* stream)
 {
     if (check_batch_io(b, io) || !U_candidates) return MPPI_EINVAL;
-    return launch_batch_select(b->d_probs, b->n, io->q, io->qd, io->target, const_cast<double*>(io->U_nominal),
+    return launch_batch_select(b->d_probs, b->d_mf, b->n, io->q, io->qd, io->target, const_cast<double*>(io->U_nominal),
                                U_candidates, costs, (hipStream_t)stream) == hipSuccess
                ? MPPI_OK
                : MPPI_EDEVICE;

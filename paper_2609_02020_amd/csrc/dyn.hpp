@@ -120,6 +120,24 @@ MPPI_HD float rsqrt_sqrt_(float x)
 #endif
 }
 MPPI_HD double rsqrt_sqrt_(double x) { return std::sqrt(x); }
+// 1 / sqrt(x)
+MPPI_HD float rsqrt_(float x) { return rcp_(rsqrt_sqrt_(x)); }
+MPPI_HD double rsqrt_(double x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    // the hardware's estimate and two Newton steps y += y (1 - x y^2) / 2 in
+    // fused operations, a third of the instructions of sqrt and a division
+    double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double e = fma_(-x * y, y, 1.0);
+        y = fma_(0.5 * y, e, y);
+    }
+    return y;
+#else
+    return 1.0 / std::sqrt(x);
+#endif
+}
 // keeps the instruction scheduler from moving code across this point (on
 // the device; nothing on the host): placed after a batch of LDS or memory
 // reads, it keeps the batch issued together ahead of its uses

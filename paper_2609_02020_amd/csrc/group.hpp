@@ -61,16 +61,32 @@
 namespace mppi {
 
 constexpr int kGroup = 8;
-// group LDS area (values of the rollout type)
-constexpr int kGxS = 16;                   // slot: S_j (6), 10 unused
-constexpr int kGxSF = 0;                   // [8][kGxS]
-constexpr int kGxRow = kGxSF + 8 * kGxS;   // [8][9]: M row j, tau - h, tau_F
-constexpr int kGxOm = kGxRow + 8 * 9;      // [8][8]: the LDL^T factor of M (row i: L below the diagonal,
+// Group LDS area (values of the rollout type).  The part that the cost part
+// of a step reads comes first: the update kernels, whose dynamics wave is
+// one step ahead of the cost wave, keep two of it (kGxPart values each) and
+// one of the rest, which only the dynamics part touches.
+constexpr int kGxSF = 0;                   // [8][6]: S_j
+constexpr int kGxTf = kGxSF + 8 * 6;       // [8]: tau_F
+constexpr int kGxH = kGxTf + 8;            // [8][12]: handoff to the cost part: q, qd, v, p_j, h_c, m_c
+                                           // (lanes 0..6); lane 7: p_ee, R_ee
+constexpr int kGxOm = kGxH + 8 * 12;       // [8][8]: the LDL^T factor of M (row i: L below the diagonal,
                                            // 1 / d_i on it), then lane j's column of the force solve's
                                            // triangular factor
-constexpr int kGxH = kGxOm + 8 * 8;        // [8][12]: handoff to the cost part: q, qd, v, p_j, h_c, m_c
-                                           // (lanes 0..6); lane 7: p_ee, R_ee
-constexpr int kGxCount = kGxH + 8 * 12;    // 424
+constexpr int kGxPart = kGxOm + 8 * 8;     // 216
+constexpr int kGxRow = kGxPart;            // [8][8]: M row j up to the diagonal
+constexpr int kGxRhs = kGxRow + 8 * 8;     // [8]: tau - h
+constexpr int kGxRows = 8 * 8 + 8;         // 72
+constexpr int kGxCount = kGxPart + kGxRows;   // 288
+// Strides between the areas of a wave's groups.  A step's reads are uniform
+// over a group (eight addresses per wave, 16 bytes each) or lane by lane
+// within its area (the collision pairs' segment ends): the eight areas start
+// on distinct banks with strides of an odd number of 32-byte units.
+template <typename R> constexpr int gx_pad(int n) { return sizeof(R) == 4 ? (n + 7) / 16 * 16 + 8 : (n + 3) / 8 * 8 + 4; }
+template <typename R> constexpr int kGxStride = gx_pad<R>(kGxCount);                        // one area
+template <typename R> constexpr int kGxPairStride = gx_pad<R>(2 * kGxPart + kGxRows);       // two cost parts, one set of rows
+static_assert(kGxStride<float> >= kGxCount && kGxStride<double> >= kGxCount, "area size");
+static_assert(kGxPairStride<float> >= 2 * kGxPart + kGxRows && kGxPairStride<double> >= 2 * kGxPart + kGxRows,
+              "area size");
 
 // Per-lane constants of the group rollout (lane 7: the EE frame, massless).
 template <typename R> struct GroupLink {
@@ -117,9 +133,9 @@ template <typename R> MPPI_HD R group_normal(uint64_t seed, uint32_t tick, uint3
 }
 
 // the perturbation recursion of noise_step for this lane's joint
-template <typename R> MPPI_HD R group_noise_step(const CostM<R>& C, const GroupLink<R>& L, R z, R du, int t)
+template <typename R> MPPI_HD R group_noise_step(R rho, const GroupLink<R>& L, R z, R du, int t)
 {
-    return (t == 0 || C.rho == R(0)) ? L.sigma * z : C.rho * du + L.sig_c * z;
+    return (t == 0 || rho == R(0)) ? L.sigma * z : rho * du + L.sig_c * z;
 }
 
 // ---------------------------------------------------------------------------
@@ -174,14 +190,13 @@ template <typename R, class G> MPPI_HD void group_fk(const G& g, const GroupLink
     scan_frames<4>(g, Q, p);
 }
 
-// The cost weights that the group's running and terminal costs read at
-// every step, held in registers: read once with the other reads of a
-// step, where reads from the cost copy in LDS inside the EE lane's branch
-// would each wait for their own round trip.
+// The cost weights that the group's running and terminal costs use at
+// every step, held in registers: reads from the cost copy in LDS inside the
+// EE lane's branch would each wait for their own round trip.
 template <typename R> struct GroupCostW {
     R W_pos[3], W_ori[3], W_force[6], W_reg[6];
     R w_q, w_qd, w_post, w_tau;
-    int has_ori;
+    int has_ori, force_mode;
 };
 template <typename R> MPPI_HD void group_cost_w(const CostM<R>& C, GroupCostW<R>& w)
 {
@@ -191,6 +206,7 @@ template <typename R> MPPI_HD void group_cost_w(const CostM<R>& C, GroupCostW<R>
     for (int a = 0; a < 6; ++a) { w.W_force[a] = C.W_force[a]; w.W_reg[a] = C.W_reg[a]; }
     w.w_q = C.w_q; w.w_qd = C.w_qd; w.w_post = C.w_post; w.w_tau = C.w_tau;
     w.has_ori = C.has_ori;
+    w.force_mode = C.force_mode;
 }
 
 // pose terms of Eqs. 9-11 from the EE frame (R_ee = R_n R_ee,fixed)
@@ -237,8 +253,7 @@ template <int S, typename R, class G> MPPI_HD void group_mgs_step(const G& g, R*
         n2 = fma_(u[i], u[i], n2);
         d = fma_(u[i], col[i], d);
     }
-    const R r = rsqrt_sqrt_(n2);
-    idg[S] = rcp_(r);
+    idg[S] = rsqrt_(n2);
     Rc[S] = d * idg[S];
     const R coef = g.j > S ? d * idg[S] * idg[S] : R(0);
 #pragma unroll
@@ -254,19 +269,19 @@ template <typename R> struct GroupStepOut {
 };
 
 // M = L D L^T (unit lower L, lower triangle in Lm, 1/d in id) of the rows
-// gathered in the group area, in every lane; b0 (may be null): the
-// right-hand side tau - h of the rows.
+// gathered in the group area (rows: its kGxRow part), in every lane; b0 (may
+// be null): the right-hand side tau - h of the rows.
 template <typename R> struct GroupFactor {
     R Lm[NJ][NJ];
     R id[NJ];
 };
-template <typename R> MPPI_HD void group_factor(const R* X, GroupFactor<R>& f, R* b0)
+template <typename R> MPPI_HD void group_factor(const R* rows, GroupFactor<R>& f, R* b0)
 {
 #pragma unroll
     for (int i = 0; i < NJ; ++i) {
 #pragma unroll
-        for (int c = 0; c <= i; ++c) f.Lm[i][c] = X[kGxRow + i * 9 + c];
-        if (b0) b0[i] = X[kGxRow + i * 9 + 7];
+        for (int c = 0; c <= i; ++c) f.Lm[i][c] = rows[i * 8 + c];
+        if (b0) b0[i] = rows[kGxRhs - kGxRow + i];
     }
 #pragma unroll
     for (int k = 0; k < NJ; ++k) {
@@ -287,19 +302,21 @@ template <typename R> MPPI_HD void group_factor(const R* X, GroupFactor<R>& f, R
 // lane's qdd (0 in lane 7); p, Q receive this lane's frame (lane 7: the EE
 // pose).  tau: this lane's joint torque (sampled torque plus any
 // joint-space external torque); v: the sampled torque (tau_F).
-// FDYN: the input of the force estimate that the rows do not hold (tau_F
-// in column 8 of the rows) is formed here, on the
-// dynamics chain; otherwise group_cost forms it from the handoff.  The
+// FDYN: the input of the force estimate that the rows do not hold (tau_F)
+// is formed here, on the dynamics chain; otherwise group_cost forms it from the handoff.  The
 // update kernel chooses FDYN when the cost part also carries the collision
 // pairs, so that neither part runs both.
 // wrench: when given, a further world wrench [force; moment] at the EE
 // point, acting on the EE lane at this step's state (J(q)^T W on the joints).
+// rows: the kGxRow part of the area where it is not kept behind X.
 template <typename R, bool FORCE, class G, bool FDYN = false, bool HANDOFF = false>
 MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, const R* grav, int ext, R q, R qd,
-                         R tau, R v, R* X, GroupFactor<R>* fac, R* p, R* Q, const R* wrench = nullptr)
+                         R tau, R v, R* X, GroupFactor<R>* fac, R* p, R* Q, const R* wrench = nullptr,
+                         R* rows = nullptr)
 {
     const int j = g.j;
     const bool ee = j == kGroup - 1;
+    if (!rows) rows = X + kGxRow;
     // the wall's constants, read ahead of the chain that uses them
     R wn[3], wd0 = R(0), wk = R(0), wc = R(0);
     if (ext == EXTW_WALL) {
@@ -411,7 +428,7 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
     }
 
     // ---- gather S (Ic S stays in this lane)
-    R* slot = X + kGxSF + j * kGxS;
+    R* slot = X + kGxSF + j * 6;
 #pragma unroll
     for (int a = 0; a < 3; ++a) { slot[a] = z[a]; slot[3 + a] = pz[a]; }
     if (FORCE && FDYN) {
@@ -423,18 +440,18 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
             cross3(In, ag, ha);
             tf = v - (dot3(z, ha) + In[3] * dot3(pz, ag));
         }
-        X[kGxRow + j * 9 + 8] = ee ? R(0) : tf;
+        X[kGxTf + j] = ee ? R(0) : tf;
     }
     g.sync();
     // row j of M up to the diagonal: M_jc = S_c . (Ic S)_j (c <= j), plus
     // the armature; every lane reads the slots at the same offsets and
-    // multiplies by its own Ic S.  Above the diagonal the same products
-    // are not M (nothing reads that part of the rows).
+    // multiplies by its own Ic S.  Above the diagonal, and in the EE lane,
+    // the same products are not M (nothing reads that part of the rows).
     R Sc[NJ][6], row[NJ];
 #pragma unroll
     for (int c = 0; c < NJ; ++c)
 #pragma unroll
-        for (int a = 0; a < 6; ++a) Sc[c][a] = X[kGxSF + c * kGxS + a];
+        for (int a = 0; a < 6; ++a) Sc[c][a] = X[kGxSF + c * 6 + a];
     sched_fence();   // the 42 reads in one round trip
 #pragma unroll
     for (int c = 0; c < NJ; ++c) {
@@ -442,35 +459,26 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
         R s = S[0] * Fm[0] + S[1] * Fm[1] + S[2] * Fm[2] + S[3] * Fm[3] + S[4] * Fm[4] + S[5] * Fm[5];
         row[c] = s + (c == j ? L.arm : R(0));
     }
-    // the EE lane's slot holds no motion subspace: its rows are 0
-    if (ee) {
 #pragma unroll
-        for (int c = 0; c < NJ; ++c) row[c] = R(0);
-    }
-#pragma unroll
-    for (int c = 0; c < NJ; ++c) X[kGxRow + j * 9 + c] = row[c];
-    X[kGxRow + j * 9 + 7] = tau - hq;
+    for (int c = 0; c < NJ; ++c) rows[j * 8 + c] = row[c];
+    rows[kGxRhs - kGxRow + j] = tau - hq;
     g.sync();
 
     // ---- Eq. 6: qdd = L^-T D^-1 L^-1 (tau + tau_ext - h)
     GroupFactor<R> local;
     GroupFactor<R>& F = fac ? *fac : local;
     R b0[NJ], x[NJ];
-    group_factor(X, F, b0);
+    group_factor(rows, F, b0);
     // handoff to the cost part: pre-step q, qd, v, the joint origin and the
     // subtree's mass and first moment (lanes 0..6), the EE pose (lane 7);
     // written once the rows are read, so that the row reads do not queue
     // behind these writes
     R* h = X + kGxH + j * 12;
-    if (ee) {
+    {
+        const R own[12] = {q, qd, v, p[0], p[1], p[2], In[0], In[1], In[2], In[3], R(0), R(0)};
+        const R eep[12] = {p[0], p[1], p[2], Q[0], Q[1], Q[2], Q[3], Q[4], Q[5], Q[6], Q[7], Q[8]};
 #pragma unroll
-        for (int a = 0; a < 3; ++a) h[a] = p[a];
-#pragma unroll
-        for (int a = 0; a < 9; ++a) h[3 + a] = Q[a];
-    } else {
-        h[0] = q; h[1] = qd; h[2] = v;
-        h[3] = p[0]; h[4] = p[1]; h[5] = p[2];
-        if (FORCE && !FDYN) { h[6] = In[0]; h[7] = In[1]; h[8] = In[2]; h[9] = In[3]; }
+        for (int a = 0; a < 12; ++a) h[a] = ee ? eep[a] : own[a];
     }
 #pragma unroll
     for (int i = 0; i < NJ; ++i) {
@@ -513,17 +521,15 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
 // from the joint origins and the EE point in the handoff).  Uses the kGxOm
 // part of X.
 template <typename R, bool FORCE, bool COLL, class G, bool FDYN = false, bool HANDOFF = false>
-MPPI_HD R group_cost(const G& g, const GroupLink<R>& L, const CostM<R>& C, const TargetM<R>& tg, const R* grav,
-                     R* X, const GroupFactor<R>* fac, R q, R qd, R v, const R* pee, const R* Re,
-                     R* Fout = nullptr)
+MPPI_HD R group_cost(const G& g, const GroupLink<R>& L, const CostM<R>& C, const GroupCostW<R>& W,
+                     const TargetM<R>& tg, const R* grav, R* X, const GroupFactor<R>* fac, R q, R qd, R v,
+                     const R* pee, const R* Re, R* Fout = nullptr)
 {
     const int j = g.j;
     const bool ee = j == kGroup - 1;
-    GroupCostW<R> W;
-    group_cost_w(C, W);
     R sj[6];   // this lane's motion subspace (the gravity torque of tau_F)
 #pragma unroll
-    for (int a = 0; a < 6; ++a) sj[a] = X[kGxSF + j * kGxS + a];
+    for (int a = 0; a < 6; ++a) sj[a] = X[kGxSF + j * 6 + a];
     sched_fence();   // with the handoff reads: one round trip
     R ell = R(0);
     if (COLL) {
@@ -561,8 +567,8 @@ MPPI_HD R group_cost(const G& g, const GroupLink<R>& L, const CostM<R>& C, const
             R ha[3];
             cross3(hj + 6, ag, ha);
             const R tg0 = v - (dot3(sj, ha) + hj[9] * dot3(sj + 3, ag));
-            const R tf = C.force_mode == 0 ? tg0 : v;
-            X[kGxRow + j * 9 + 8] = ee ? R(0) : tf;
+            const R tf = W.force_mode == 0 ? tg0 : v;
+            X[kGxTf + j] = ee ? R(0) : tf;
         }
         // row r of the EE Jacobian about p_ee at joint i: z_i (r < 3), then
         // (p_i - p_ee) x z_i, i.e. component r of the motion subspace S_i
@@ -570,7 +576,7 @@ MPPI_HD R group_cost(const G& g, const GroupLink<R>& L, const CostM<R>& C, const
         const int r = j < 6 ? j : 5;
         R Jr[NJ];
 #pragma unroll
-        for (int i = 0; i < NJ; ++i) Jr[i] = X[kGxSF + i * kGxS + r];
+        for (int i = 0; i < NJ; ++i) Jr[i] = X[kGxSF + i * 6 + r];
         g.sync();
         GroupFactor<R> local;
         if (!fac && HANDOFF) {
@@ -582,12 +588,12 @@ MPPI_HD R group_cost(const G& g, const GroupLink<R>& L, const CostM<R>& C, const
                 local.id[i] = X[kGxOm + i * 8 + i];
             }
         } else if (!fac) {
-            group_factor(X, local, (R*)nullptr);
+            group_factor(X + kGxRow, local, (R*)nullptr);
         }
         const GroupFactor<R>& Fc = fac ? *fac : local;
         R bF[NJ];
 #pragma unroll
-        for (int i = 0; i < NJ; ++i) bF[i] = X[kGxRow + i * 9 + 8];
+        for (int i = 0; i < NJ; ++i) bF[i] = X[kGxTf + i];
         // ---- lane r < 6 solves for row r of J, lane 6 (and 7) for tau_F;
         // scaled by D^-1/2 that is column j of [A^T | y] with Omega = A A^T
         // and J M^-1 tau_F = A y (M = L D L^T, A^T = D^-1/2 L^-1 J^T)
@@ -653,7 +659,9 @@ MPPI_HD R group_step(const G& g, const GroupLink<R>& L, const CostM<R>& C, const
     GroupFactor<R> fac;
     R p[3], Q[9], F[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
     qdd = group_dynamics<R, FORCE, G, COLL>(g, L, C, grav, ext, q, qd, tau, v, g.shm, &fac, p, Q);
-    const R ell = group_cost<R, FORCE, COLL, G, COLL>(g, L, C, tg, grav, g.shm, &fac, q, qd, v, p, Q, F);
+    GroupCostW<R> W;
+    group_cost_w(C, W);
+    const R ell = group_cost<R, FORCE, COLL, G, COLL>(g, L, C, W, tg, grav, g.shm, &fac, q, qd, v, p, Q, F);
     if (dbg) {
         dbg->qdd = qdd;
 #pragma unroll
@@ -695,10 +703,12 @@ MPPI_HD R group_rollout(const G& g, const GroupLink<R>& L, const CostM<R>& C, co
     const int jc = j < NJ ? j : NJ - 1;
     const int ext = C.ext_mode == EXTW_WALL ? EXTW_WALL : EXTW_NONE;
     const R dt = C.dt;
+    GroupCostW<R> W;
+    group_cost_w(C, W);
     R du = R(0), S = R(0);
     for (int t = 0; t < T; ++t) {
         const R z = group_normal<R>(seed, tick, k, (uint32_t)t, j);
-        du = group_noise_step(C, L, z, du, t);
+        du = group_noise_step(C.rho, L, z, du, t);
         if (noise_out && j < NJ) noise_out[(size_t)(t * NJ + j) * noise_stride] = du;
         if (noise_lds && j < NJ) noise_lds[(t * NJ + j) * lds_stride] = du;
         const R v = (R(Us[t * NJ + jc]) + du) * L.live;
@@ -709,7 +719,7 @@ MPPI_HD R group_rollout(const G& g, const GroupLink<R>& L, const CostM<R>& C, co
             // registers across the cost part
             R p[3], Q[9];
             qdd = group_dynamics<R, FORCE, G, COLL, true>(g, L, C, grav, ext, q, qd, v + te, v, g.shm, nullptr, p, Q);
-            S += group_cost<R, FORCE, COLL, G, COLL, true>(g, L, C, tg, grav, g.shm, nullptr, q, qd, v, p, Q);
+            S += group_cost<R, FORCE, COLL, G, COLL, true>(g, L, C, W, tg, grav, g.shm, nullptr, q, qd, v, p, Q);
         } else {
             S += group_step<R, FORCE, G, COLL>(g, L, C, tg, grav, ext, q, qd, v + te, v, qdd);
         }

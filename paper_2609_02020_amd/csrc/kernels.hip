@@ -1,7 +1,7 @@
 // kernels.hip -- the MPPI hot path on gfx950.
 //
-//   update_group_kernel + group_merge_kernel (a1-a12, the default for FP32
-//                   rollouts): eight lanes per sample (group.hpp) on
+//   update_group_kernel + group_merge_kernel (a1-a12, the default for
+//                   rollouts of the articulated-body route): eight lanes per sample (group.hpp) on
 //                   dynamics/cost wave pairs, workgroup partials of Eq. 4,
 //                   merged by a second launch.
 //   update_split_kernel (two waves per 64 samples) and
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(128) void update_split_kernel(
     if (lane == 0) *counter = 0u;
 }
 
-// One MPPI update with eight lanes per sample (group.hpp): lane j of a
+// One MPPI update with eight lanes per sample (group.hpp), FP32 or FP64: lane j of a
 // group holds joint j, lane 7 the EE frame, and every group of samples is
 // served by two waves: a dynamics wave (kinematics, inertias, the rows of M,
 // the LDL^T solve of Eq. 6 and the Euler step: the sequential chain of a
@@ -405,108 +405,142 @@ template <typename R> struct DevGroup {
     __device__ void sync() const { wave_sync(); }
 };
 
-template <typename A, bool FORCE, bool COLL>
-__global__ __launch_bounds__(kGroupThreads) void update_group_kernel(
-    const ModelM<float>* __restrict__ Mp, const CostM<float>* __restrict__ Cp, const double* __restrict__ q0,
-    const double* __restrict__ qd0, const double* __restrict__ target, const double* U_nom,
-    uint64_t seed, uint32_t tick, int K, int T, double lambda, float* __restrict__ noise,
-    float* __restrict__ S, int merge, int lds_noise, A* __restrict__ parts)
+// The two roles of a pair of waves, each with its own loop, so that a
+// wave's registers hold only its own constants (read once, before the
+// loop).  Both pass T + 2 barriers: one after the set-up, one per step
+// s = 0 .. T.  `role` of the callers is a scalar, so each wave branches to
+// its loop as a whole.
+//
+// Dynamics: step s < T from the torque v = torque(s) into the parity s & 1
+// of the pair area X; in step T, while the cost wave evaluates step T - 1,
+// the terminal cost phi(x_T) of the target tgs, this lane's share into *tS.
+template <typename R, bool FORCE, bool COLL, typename V>
+__device__ __forceinline__ void group_dynamics_loop(const ModelM<R>& M, const CostM<R>& Cg, const CostM<R>& C, int j,
+                                                    const double* q0, const double* qd0, int T, R* X, V torque,
+                                                    const TargetM<R>& tgs, R* tS)
 {
-    extern __shared__ char dyn_lds[];   // lds_noise: du tile [7T][kGroupTile]
-    __shared__ float gx[2][kGroupSamples][kGxCount];
-    __shared__ float nb[2][kGroupSamples][8];
-    __shared__ float Us[kMaxT * NJ];
-    __shared__ CostM<float> Csh;
-    __shared__ float sS[kGroupSamples];
+    GroupLink<R> L;
+    group_link(M, Cg, j, L);
+    const R grav[3] = {M.g[0], M.g[1], M.g[2]};
+    R q = R(0), qd = R(0), te = R(0);
+    {
+        R qa[NJ], qda[NJ], tea[NJ];
+#pragma unroll
+        for (int i = 0; i < NJ; ++i) { qa[i] = R(q0[i]); qda[i] = R(qd0[i]); tea[i] = R(0); }
+        if (Cg.ext_mode == EXTW_CONST) const_ext_torque(M, Cg, qa, tea);
+#pragma unroll
+        for (int i = 0; i < NJ; ++i)
+            if (i == j) { q = qa[i]; qd = qda[i]; te = tea[i]; }
+    }
+    const int ext = Cg.ext_mode == EXTW_WALL ? EXTW_WALL : EXTW_NONE;
+    const R dt = Cg.dt;
+    CostM<R> W;   // what group_dynamics reads of the cost, in registers
+#pragma unroll
+    for (int a = 0; a < 3; ++a) W.wall_n[a] = Cg.wall_n[a];
+    W.wall_d0 = Cg.wall_d0;
+    W.wall_k = Cg.wall_k;
+    W.wall_c = Cg.wall_c;
+    W.force_mode = Cg.force_mode;
+    const DevGroup<R> g{j, X};
+    __syncthreads();
+    for (int s = 0; s < T; ++s) {
+        const R v = torque(s) * L.live;
+        R p[3], Q[9];
+        const R qdd = group_dynamics<R, FORCE, DevGroup<R>, COLL, true>(
+            g, L, W, grav, ext, q, qd, v + te, v, X + (s & 1) * kGxPart, nullptr, p, Q, nullptr, X + 2 * kGxPart);
+        qd += qdd * dt;
+        q += qd * dt;
+        __syncthreads();
+    }
+    *tS = group_terminal(g, L, C, tgs, q, qd);   // lane 7: q = qd = 0
+    __syncthreads();
+}
+// Cost: draws the perturbation of step s + 1 (draw(s + 1), s + 1 < T) and
+// evaluates step s - 1 from the pair area; returns this lane's share of the
+// running cost.  One lane of the caller's workgroup (keeps != 0) leaves the
+// target in tgs for the dynamics waves.
+template <typename R, bool FORCE, bool COLL, typename D>
+__device__ __forceinline__ R group_cost_loop(const ModelM<R>& M, const CostM<R>& Cg, const CostM<R>& C, int j,
+                                             const double* target, int T, R* X, D draw, TargetM<R>& tgs, bool keeps)
+{
+    GroupLink<R> L;
+    group_link(M, Cg, j, L);
+    const R grav[3] = {M.g[0], M.g[1], M.g[2]};
+    GroupCostW<R> W;
+    group_cost_w(Cg, W);
+    TargetM<R> tg;
+    make_target(target, tg);
+    if (keeps) tgs = tg;
+    draw(0, L);
+    R Sl = R(0);
+    __syncthreads();
+    for (int s = 0; s <= T; ++s) {
+        if (s + 1 < T) draw(s + 1, L);
+        if (s >= 1) {
+            R* Xs = X + ((s - 1) & 1) * kGxPart;
+            const DevGroup<R> g{j, Xs};
+            const R* h = Xs + kGxH + j * 12;
+            R pe[3], Re[9];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) pe[a] = h[a];
+#pragma unroll
+            for (int a = 0; a < 9; ++a) Re[a] = h[3 + a];
+            Sl += group_cost<R, FORCE, COLL, DevGroup<R>, COLL, true>(g, L, C, W, tg, grav, Xs, nullptr, h[0], h[1], h[2],
+                                                                      pe, Re);
+        }
+        __syncthreads();
+    }
+    return Sl;
+}
+
+template <typename R, typename A, bool FORCE, bool COLL>
+__global__ __launch_bounds__(kGroupThreads, sizeof(R) == 8 ? 2 : 1) void update_group_kernel(
+    const ModelM<R>* __restrict__ Mp, const CostM<R>* __restrict__ Cp, const double* __restrict__ q0,
+    const double* __restrict__ qd0, const double* __restrict__ target, const double* U_nom,
+    uint64_t seed, uint32_t tick, int K, int T, double lambda, R* __restrict__ noise,
+    R* __restrict__ S, int merge, int lds_noise, A* __restrict__ parts)
+{
+    extern __shared__ __align__(16) char dyn_lds[];   // U_nom [7T], then (lds_noise) the du tile [7T][kGroupTile]
+    __shared__ __align__(16) R gx[kGroupSamples][kGxPairStride<R>];
+    __shared__ R nb[2][kGroupSamples][8];
+    __shared__ CostM<R> Csh;
+    __shared__ TargetM<R> tgs;
+    __shared__ R sS[kGroupSamples];
     __shared__ A vs[kGroupPairs][kGroupSteps * 8];
     __shared__ A wsm[kGroupSamples];
-    __shared__ float tS[kGroupSamples][8];   // the terminal cost's lane shares
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ R tS[kGroupSamples][8];   // the terminal cost's lane shares
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool dyn = wave < kGroupPairs;   // waves 0.. P-1: dynamics, P.. 2P-1: cost
     const int pw = dyn ? wave : wave - kGroupPairs;
     const int j = group_joint(lane), grp = pw * 8 + group_sample(lane), jc = j < NJ ? j : NJ - 1;
     const int k = blockIdx.x * kGroupSamples + grp;
     const bool valid = k < K;
-    // set-up from global memory (the cost constants from Cp directly, so that
-    // every load is issued before the first barrier)
-    const ModelM<float>& M = *Mp;
-    GroupLink<float> L;
-    group_link(M, *Cp, j, L);
-    const float grav[3] = {M.g[0], M.g[1], M.g[2]};
-    TargetM<float> tg;
-    make_target(target, tg);   // the cost wave's running cost, the dynamics wave's terminal cost
-    float q = 0.0f, qd = 0.0f, te = 0.0f;
-    if (dyn) {
-        float qa[NJ], qda[NJ], tea[NJ];
-#pragma unroll
-        for (int i = 0; i < NJ; ++i) { qa[i] = float(q0[i]); qda[i] = float(qd0[i]); tea[i] = 0.0f; }
-        if (Cp->ext_mode == EXTW_CONST) const_ext_torque(M, *Cp, qa, tea);
-#pragma unroll
-        for (int i = 0; i < NJ; ++i)
-            if (i == j) { q = qa[i]; qd = qda[i]; te = tea[i]; }
-    }
+    R* Us = reinterpret_cast<R*>(dyn_lds);
+    R* tile = Us + T * NJ;
     if (wave == 0) wave_copy(&Csh, Cp, lane);
-    for (int i = tid; i < T * NJ; i += blockDim.x) Us[i] = float(U_nom[i]);
-    const CostM<float>& C = Csh;
-    float* tile = reinterpret_cast<float*>(dyn_lds);
-    float* nz_out = (valid && noise && j < NJ) ? noise + k : nullptr;
-    float* nz_lds = (lds_noise && j < NJ) ? tile + grp : nullptr;
-    const int ext = Cp->ext_mode == EXTW_WALL ? EXTW_WALL : EXTW_NONE;
-
-    // the cost wave draws du of step t; du carries the AR(1) recursion
-    float du = 0.0f, Sl = 0.0f;
-    auto draw = [&](int t) {
-        du = group_noise_step(C, L, group_normal<float>(seed, tick, (uint32_t)k, (uint32_t)t, j), du, t);
-        nb[t & 1][grp][j] = du;
-        if (nz_out) nz_out[(size_t)(t * NJ + j) * K] = du;
-        if (nz_lds) nz_lds[(t * NJ + j) * kGroupTile] = du;
-    };
-    // step 0's draw needs only this lane's sigma (not the LDS cost copy)
-    if (!dyn) draw(0);
-    const float dt = Cp->dt;   // in a register: the step's last operation reads it
-    __syncthreads();
-    for (int s = 0; s <= T; ++s) {
-        if (dyn) {
-            if (s < T) {
-                float* X = gx[s & 1][grp];
-                const DevGroup<float> g{j, X};
-                const float v = (Us[s * NJ + jc] + nb[s & 1][grp][j]) * L.live;
-                float p[3], Q[9];
-                const float qdd = group_dynamics<float, FORCE, DevGroup<float>, COLL, true>(g, L, C, grav, ext, q, qd, v + te, v, X,
-                                                                               nullptr, p, Q);
-                qd += qdd * dt;
-                q += qd * dt;
-            } else {
-                // phi(x_T) (lane 7: q = qd = 0), while the cost wave
-                // evaluates step T - 1
-                const DevGroup<float> g{j, gx[s & 1][grp]};
-                tS[grp][j] = group_terminal(g, L, C, tg, q, qd);
-            }
-        } else {
-            if (s + 1 < T) draw(s + 1);
-            if (s >= 1) {
-                float* X = gx[(s - 1) & 1][grp];
-                const DevGroup<float> g{j, X};
-                const float* h = X + kGxH + j * 12;
-                float pe[3], Re[9];
-#pragma unroll
-                for (int a = 0; a < 3; ++a) pe[a] = h[a];
-#pragma unroll
-                for (int a = 0; a < 9; ++a) Re[a] = h[3 + a];
-                Sl += group_cost<float, FORCE, COLL, DevGroup<float>, COLL, true>(g, L, C, tg, grav, X, nullptr, h[0], h[1], h[2], pe,
-                                                                     Re);
-            }
-        }
-        __syncthreads();
-    }
-    // the terminal cost from the dynamics wave (ordered by the last barrier)
-    if (!dyn) {
-        const DevGroup<float> g{j, gx[T & 1][grp]};
-        Sl += tS[grp][j];
-        const float tot = g.sum(Sl);
-        float sv = INFINITY;
+    for (int i = tid; i < T * NJ; i += blockDim.x) Us[i] = R(U_nom[i]);
+    if (dyn) {
+        group_dynamics_loop<R, FORCE, COLL>(
+            *Mp, *Cp, Csh, j, q0, qd0, T, gx[grp], [&](int s) { return Us[s * NJ + jc] + nb[s & 1][grp][j]; }, tgs,
+            &tS[grp][j]);
+    } else {
+        R* nz_out = (valid && noise && j < NJ) ? noise + k : nullptr;
+        R* nz_lds = (lds_noise && j < NJ) ? tile + grp : nullptr;
+        const R rho = Cp->rho;
+        R du = R(0);   // carries the AR(1) recursion
+        auto draw = [&](int t, const GroupLink<R>& L) {
+            du = group_noise_step(rho, L, group_normal<R>(seed, tick, (uint32_t)k, (uint32_t)t, j), du, t);
+            nb[t & 1][grp][j] = du;
+            if (nz_out) nz_out[(size_t)(t * NJ + j) * K] = du;
+            if (nz_lds) nz_lds[(t * NJ + j) * kGroupTile] = du;
+        };
+        const R Sl = group_cost_loop<R, FORCE, COLL>(*Mp, *Cp, Csh, j, target, T, gx[grp], draw, tgs, lane == 0 && pw == 0);
+        // the terminal cost from the dynamics wave (ordered by the last barrier)
+        const DevGroup<R> g{j, nullptr};
+        const R tot = g.sum(Sl + tS[grp][j]);
+        R sv = R(INFINITY);
         if (valid) {
-            sv = finite_(tot) ? tot : INFINITY;
+            sv = finite_(tot) ? tot : R(INFINITY);
             if (j == 0) S[k] = sv;
         }
         if (j == 0) sS[grp] = sv;
@@ -526,23 +560,45 @@ __global__ __launch_bounds__(kGroupThreads) void update_group_kernel(
     A* part = parts + (size_t)gridDim.x * 2 + (size_t)blockIdx.x * (T * NJ);
     if (lds_noise) {
         for (int r = tid; r < T * NJ; r += blockDim.x) {
-            const float* row = tile + r * kGroupTile;
+            const R* row = tile + r * kGroupTile;
             A acc = A(0);
 #pragma unroll
             for (int i = 0; i < kGroupSamples; ++i) acc += wsm[i] * A(row[i]);
+            part[r] = acc;
+        }
+    } else if (sizeof(R) == 8 && noise) {
+        // this workgroup's columns of the global noise, which it wrote itself
+        // (ordered by the barriers above), summed in the order of the
+        // regenerated sums below: the same bits with and without the buffer
+#pragma clang fp contract(off)
+        const int k0 = blockIdx.x * kGroupSamples, nk = min(kGroupSamples, K - k0);
+        for (int r = tid; r < T * NJ; r += blockDim.x) {
+            const R* row = noise + (size_t)r * K + k0;
+            A x[kGroupSamples];
+#pragma unroll
+            for (int i = 0; i < kGroupSamples; ++i) x[i] = i < nk ? wsm[i] * A(row[i]) : A(0);
+            A acc = A(0);
+#pragma unroll
+            for (int w = 0; w < kGroupPairs; ++w) {
+                const A* y = x + 8 * w;
+                acc += ((y[0] + y[1]) + (y[2] + y[3])) + ((y[4] + y[5]) + (y[6] + y[7]));
+            }
             part[r] = acc;
         }
     } else {
         // regenerated noise: the cost waves' lanes reduce w du over their
         // wave's 8 samples of each joint, then the pairs are summed
         const A wgt = wsm[grp];
-        float dr = 0.0f;
+        GroupLink<R> L;
+        group_link(*Mp, *Cp, j, L);
+        const R rho = Cp->rho;
+        R dr = R(0);
         for (int t0 = 0; t0 < T; t0 += kGroupSteps) {
             const int nt = min(kGroupSteps, T - t0);
             if (!dyn) {
                 for (int tt = 0; tt < nt; ++tt) {
                     const int t = t0 + tt;
-                    dr = group_noise_step(C, L, group_normal<float>(seed, tick, (uint32_t)k, (uint32_t)t, j), dr, t);
+                    dr = group_noise_step(rho, L, group_normal<R>(seed, tick, (uint32_t)k, (uint32_t)t, j), dr, t);
                     // over the wave's 8 samples (lane bits 0, 4, 5)
                     A x = wgt * A(dr);
                     x += __shfl_xor(x, 1);
@@ -847,7 +903,7 @@ __device__ void group_tile_partial(const float* sS, A* wsm, A (*vs)[kGroupSteps 
         const int nt = min(kGroupSteps, T - t0);
         for (int tt = 0; tt < nt; ++tt) {
             const int t = t0 + tt;
-            dr = group_noise_step(C, L, group_normal<float>(seed, tick, k, (uint32_t)t, j), dr, t);
+            dr = group_noise_step(C.rho, L, group_normal<float>(seed, tick, k, (uint32_t)t, j), dr, t);
             // over the wave's 8 samples (lane bits 0, 4, 5)
             A x = wgt * A(dr);
             x += __shfl_xor(x, 1);
@@ -882,7 +938,7 @@ __global__ __launch_bounds__(64 * kBatchGroupWaves) void batch_group_kernel(
     const uint64_t* __restrict__ seeds, const uint64_t* __restrict__ tickp, int iter, int niter,
     double* __restrict__ parts)
 {
-    __shared__ float gx[kBatchGroupWaves * 8][kGxCount];
+    __shared__ __align__(16) float gx[kBatchGroupWaves * 8][kGxStride<float>];
     __shared__ float Us[kMaxTBatch * NJ];
     __shared__ CostM<float> Csh;
     __shared__ float sS[64];
@@ -1129,7 +1185,7 @@ __global__ __launch_bounds__(64) void plant_kernel(const ModelM<double>* __restr
                                                    const CostM<double>* __restrict__ Cp, double* q, double* qd,
                                                    const double* u, double dt, int substeps, const double* wrench)
 {
-    __shared__ double X[8][kGxCount];
+    __shared__ __align__(16) double X[8][kGxStride<double>];
     const int grp = group_sample(threadIdx.x);
     // every group steps the one problem (converged waves), the first writes it
     plant_advance(PlantProblem{Mp, Cp, u, q, qd}, threadIdx.x, grp == 0, dt, substeps, wrench, X[grp]);
@@ -1175,7 +1231,7 @@ __global__ void ee_pose_kernel(const ModelM<double>* __restrict__ Mp, const doub
 __global__ __launch_bounds__(64) void batch_plant_kernel(const BatchProblem* __restrict__ probs, int n, double* q,
                                                          double* qd, const double* U_new, double dt, int substeps)
 {
-    __shared__ double X[8][kGxCount];
+    __shared__ __align__(16) double X[8][kGxStride<double>];
     const int grp = group_sample(threadIdx.x), i = blockIdx.x * 8 + grp, p = min(i, n - 1);
     const BatchProblem& Pb = probs[p];
     plant_advance(PlantProblem{Pb.model64, Pb.cost64, U_new + Pb.u_off, q + p * NJ, qd + p * NJ}, threadIdx.x, i < n,
@@ -1227,9 +1283,10 @@ __global__ void batch_warm_start_kernel(const BatchProblem* __restrict__ probs, 
 // us, 215 us with the two rollouts on two lanes of a wave (one lane each,
 // 1.3 KB of scratch).
 template <typename R> struct SelectShared {
-    alignas(16) R gx[2][2][kGxCount];   // [step parity][sample]
+    alignas(16) R gx[2][kGxPairStride<R>];
     alignas(16) CostM<R> C;
     R Us[2][kMaxT * NJ];
+    TargetM<R> tgs;
     R tS[2][8];             // the terminal cost's lane shares
     R sc[2];
 };
@@ -1241,60 +1298,19 @@ __device__ __forceinline__ void select_two(const ModelM<R>& M, const CostM<R>& C
                            SelectShared<R>& sh)
 {
     const int tid = threadIdx.x, lane = tid & 63;
-    const bool dyn = tid < 64;
     const int j = group_joint(lane), seq = lane & 1, jc = j < NJ ? j : NJ - 1;
-    if (dyn) wave_copy(&sh.C, &Cg, lane);
+    if (tid < 64) wave_copy(&sh.C, &Cg, lane);
     for (int i = tid; i < T * NJ; i += kSelectThreads) {
         sh.Us[0][i] = R(U_nom[i]);
         sh.Us[1][i] = R(U_cand[i]);
     }
-    GroupLink<R> L;
-    group_link(M, Cg, j, L);
-    const R grav[3] = {M.g[0], M.g[1], M.g[2]};
-    TargetM<R> tg;
-    make_target(target, tg);
-    R q = R(0), qd = R(0), te = R(0);
-    if (dyn) {
-        R qa[NJ], qda[NJ], tea[NJ];
-#pragma unroll
-        for (int i = 0; i < NJ; ++i) { qa[i] = R(q0[i]); qda[i] = R(qd0[i]); tea[i] = R(0); }
-        if (Cg.ext_mode == EXTW_CONST) const_ext_torque(M, Cg, qa, tea);
-#pragma unroll
-        for (int i = 0; i < NJ; ++i)
-            if (i == j) { q = qa[i]; qd = qda[i]; te = tea[i]; }
-    }
-    const int ext = Cg.ext_mode == EXTW_WALL ? EXTW_WALL : EXTW_NONE;
-    const R dt = Cg.dt;
-    R Sl = R(0);
-    __syncthreads();
-    for (int s = 0; s <= T; ++s) {
-        if (dyn) {
-            const DevGroup<R> g{j, sh.gx[s & 1][seq]};
-            if (s < T) {
-                const R v = sh.Us[seq][s * NJ + jc] * L.live;
-                R p[3], Q[9];
-                const R qdd = group_dynamics<R, FORCE, DevGroup<R>, COLL, true>(g, L, sh.C, grav, ext, q, qd, v + te, v,
-                                                                                g.shm, nullptr, p, Q);
-                qd += qdd * dt;
-                q += qd * dt;
-            } else {
-                sh.tS[seq][j] = group_terminal(g, L, sh.C, tg, q, qd);
-            }
-        } else if (s >= 1) {
-            const DevGroup<R> g{j, sh.gx[(s - 1) & 1][seq]};
-            const R* h = g.shm + kGxH + j * 12;
-            R pe[3], Re[9];
-#pragma unroll
-            for (int a = 0; a < 3; ++a) pe[a] = h[a];
-#pragma unroll
-            for (int a = 0; a < 9; ++a) Re[a] = h[3 + a];
-            Sl += group_cost<R, FORCE, COLL, DevGroup<R>, COLL, true>(g, L, sh.C, tg, grav, g.shm, nullptr, h[0], h[1],
-                                                                      h[2], pe, Re);
-        }
-        __syncthreads();
-    }
-    if (!dyn) {
-        const DevGroup<R> g{j, sh.gx[0][seq]};
+    if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) {
+        group_dynamics_loop<R, FORCE, COLL>(M, Cg, sh.C, j, q0, qd0, T, sh.gx[seq],
+                                            [&](int s) { return sh.Us[seq][s * NJ + jc]; }, sh.tgs, &sh.tS[seq][j]);
+    } else {
+        const R Sl = group_cost_loop<R, FORCE, COLL>(M, Cg, sh.C, j, target, T, sh.gx[seq],
+                                                     [](int, const GroupLink<R>&) {}, sh.tgs, lane == 0);
+        const DevGroup<R> g{j, nullptr};
         const R tot = g.sum(Sl + sh.tS[seq][j]);
         if (j == 0) sh.sc[seq] = finite_(tot) ? tot : R(INFINITY);
     }
@@ -1386,17 +1402,23 @@ template <typename A, bool FORCE, bool COLL> static hipError_t update_split_t(co
     return hipGetLastError();
 }
 
-template <typename A, bool FORCE, bool COLL> static hipError_t update_group_t(const UpdateArgs& a, hipStream_t s)
+template <typename R, typename A, bool FORCE, bool COLL>
+static hipError_t update_group_t(const UpdateArgs& a, hipStream_t s)
 {
     dim3 grid((a.K + kGroupSamples - 1) / kGroupSamples);
-    float* noise = (float*)a.noise;
-    if (a.merge && !a.want_noise) noise = nullptr;
-    const size_t tile = (size_t)a.T * NJ * kGroupTile * sizeof(float);
-    const int lds_noise = a.merge && tile <= (size_t)kMaxDynLds;
-    hipLaunchKernelGGL((update_group_kernel<A, FORCE, COLL>), grid, dim3(kGroupThreads), lds_noise ? tile : 0, s,
-                       (const ModelM<float>*)a.model, (const CostM<float>*)a.cost, a.q0, a.qd0, a.target, a.U_nom,
-                       a.seed, (uint32_t)a.tick, a.K, a.T, a.lambda, noise, (float*)a.costs, a.merge, lds_noise,
-                       (A*)a.parts);
+    R* noise = (R*)a.noise;
+    const size_t rows = (size_t)a.T * NJ, tile = rows * kGroupTile * sizeof(R);
+    // FP32 keeps the workgroup's noise in LDS where it fits.  In FP64 two
+    // workgroups share a CU's LDS only without that tile, and the second wave
+    // per SIMD is worth more (K = 16384, T = 36: 363 us against 530 with the
+    // tile): the noise goes through the global buffer (the caller's or the
+    // solver's own), or is regenerated where there is none.
+    const int lds_noise = sizeof(R) == 4 && a.merge && tile <= (size_t)kMaxDynLds;
+    if (sizeof(R) == 4 && a.merge && !a.want_noise) noise = nullptr;
+    hipLaunchKernelGGL((update_group_kernel<R, A, FORCE, COLL>), grid, dim3(kGroupThreads),
+                       rows * sizeof(R) + (lds_noise ? tile : 0), s, (const ModelM<R>*)a.model,
+                       (const CostM<R>*)a.cost, a.q0, a.qd0, a.target, a.U_nom, a.seed, (uint32_t)a.tick, a.K, a.T,
+                       a.lambda, noise, (R*)a.costs, a.merge, lds_noise, (A*)a.parts);
     if (a.merge)
         hipLaunchKernelGGL((group_merge_kernel<A>), dim3((a.T * NJ + kMergeRows - 1) / kMergeRows),
                            dim3(kGroupThreads), 0, s, (const A*)a.parts,
@@ -1407,9 +1429,22 @@ template <typename A, bool FORCE, bool COLL> static hipError_t update_group_t(co
 template <bool EXPLICIT, bool COLL>
 static hipError_t update_dispatch(int precision, bool acc64, bool force, const UpdateArgs& a, hipStream_t s)
 {
-    if (!EXPLICIT && a.waves_per_group == 8 && precision == MPPI_FP32) {
-        if (force) return acc64 ? update_group_t<double, true, COLL>(a, s) : update_group_t<float, true, COLL>(a, s);
-        return acc64 ? update_group_t<double, false, COLL>(a, s) : update_group_t<float, false, COLL>(a, s);
+    // FP64 takes the lane groups too, except where one lane per sample fills
+    // the chip evenly: between the size at which its flat time (one wave per
+    // SIMD) is reached, and the 768 waves that its LDS lets the chip hold at
+    // once (contact task, T = 18 / 36, lane groups against one lane per
+    // sample: K = 4096 78 / 142 us against 396 / 778, 32768 409 / 753 against
+    // 450 / 878, 40960 492 / 907 against 466 / 910, 65536 750 / 1419 against
+    // 901 / 1782).
+    const bool lanes64 = precision == MPPI_FP64 && a.K > 36864 && a.K <= 49152;
+    if (!EXPLICIT && a.waves_per_group == 8 && !lanes64) {
+        if (precision == MPPI_FP64)
+            return force ? update_group_t<double, double, true, COLL>(a, s)
+                         : update_group_t<double, double, false, COLL>(a, s);
+        if (acc64)
+            return force ? update_group_t<float, double, true, COLL>(a, s)
+                         : update_group_t<float, double, false, COLL>(a, s);
+        return force ? update_group_t<float, float, true, COLL>(a, s) : update_group_t<float, float, false, COLL>(a, s);
     }
     if (a.waves_per_group == 8) {   // the two-wave launch where groups do not apply
         UpdateArgs b = a;

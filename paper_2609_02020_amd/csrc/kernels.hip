@@ -166,32 +166,23 @@ __device__ __forceinline__ void handoff_read(const float* h, ForceIn<float>& fi,
     for (int c = 0; c < 9; ++c) Rn[c] = h[(kHoRn + c) * 64];
 }
 
-template <typename A, bool FORCE, bool COLL>
-__global__ __launch_bounds__(128) void update_split_kernel(
-    const ModelM<float>* __restrict__ Mp, const CostM<float>* __restrict__ Cp, const double* __restrict__ q0,
-    const double* __restrict__ qd0, const double* __restrict__ target, const double* U_nom,
-    uint64_t seed, uint32_t tick, int K, int T, double lambda, float* __restrict__ noise,
-    float* __restrict__ S, int merge, int lds_noise, A* __restrict__ parts, unsigned int* __restrict__ counter,
-    double* U_new, double* __restrict__ U_shift, int* __restrict__ status)
-{
-    extern __shared__ char dyn_lds[];
-    __shared__ float hb[2][kHandoff * 64];
-    __shared__ float nb[2][NJ * 64];
-    __shared__ float Us[kMaxT * NJ];
-    __shared__ A wl[64];
-    __shared__ int last;
-    __shared__ CostM<float> Csh;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (wave == 0) wave_copy(&Csh, Cp, lane);
-    for (int i = threadIdx.x; i < T * NJ; i += blockDim.x) Us[i] = float(U_nom[i]);
-    const int k = blockIdx.x * 64 + lane;
-    float* tile = reinterpret_cast<float*>(dyn_lds);   // [rows][65] (noise) or [64][65] (regeneration)
-    float* noise_k = (noise && k < K) ? noise + k : nullptr;
-    float* tile_k = lds_noise ? tile + lane : nullptr;
-    const ModelM<float>& Mc = *Mp;
-    const CostM<float>& Cc = Csh;
-    __syncthreads();
+struct SplitShared {
+    float hb[2][kHandoff * 64];
+    float nb[2][NJ * 64];
+};
 
+// The two waves' loop over the horizon (wave: 0 or 1; both pass the
+// same barriers, the first of which orders Us and Cc): returns this lane's
+// cost on wave 1, +inf for samples past K and non-finite costs.  noise_k,
+// tile_k (either may be null): this sample's column of the global noise
+// [7T][K] and of the LDS tile [7T][kLdsRowPad].
+template <bool FORCE, bool COLL>
+__device__ __forceinline__ float split_rollout(const ModelM<float>& Mc, const CostM<float>& Cc, const double* q0,
+                                               const double* qd0, const double* target, const float* Us, int T, int K,
+                                               int k, uint64_t seed, uint32_t tick, float* noise_k, float* tile_k,
+                                               SplitShared& sh, int lane, int wave)
+{
+    __syncthreads();
     float q[NJ], qd[NJ], te[NJ];   // wave 0: the trajectory
     float du[NJ], Ssum = 0.0f;     // wave 1: the noise recursion and the cost
     TargetM<float> tg;
@@ -208,7 +199,7 @@ __global__ __launch_bounds__(128) void update_split_kernel(
         noise_step(Cc, z, du, 0);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            nb[0][j * 64 + lane] = du[j];
+            sh.nb[0][j * 64 + lane] = du[j];
             if (noise_k) noise_k[(size_t)j * K] = du[j];
             if (tile_k) tile_k[j * kLdsRowPad] = du[j];
         }
@@ -223,11 +214,11 @@ __global__ __launch_bounds__(128) void update_split_kernel(
                 float v[NJ], tau[NJ];
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
-                    v[j] = Us[s * NJ + j] + nb[s & 1][j * 64 + lane];
+                    v[j] = Us[s * NJ + j] + sh.nb[s & 1][j * 64 + lane];
                     tau[j] = v[j] + te[j];
                 }
                 StepOut<float> o;
-                float* h = &hb[s & 1][lane];
+                float* h = &sh.hb[s & 1][lane];
                 dyn_step<float, FORCE>(M, C, ext, q, qd, tau, v, o, h, 64);
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
@@ -254,7 +245,7 @@ __global__ __launch_bounds__(128) void update_split_kernel(
                 noise_step(C, z, du, s + 1);
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
-                    nb[(s + 1) & 1][j * 64 + lane] = du[j];
+                    sh.nb[(s + 1) & 1][j * 64 + lane] = du[j];
                     if (noise_k) noise_k[(size_t)((s + 1) * NJ + j) * K] = du[j];
                     if (tile_k) tile_k[((s + 1) * NJ + j) * kLdsRowPad] = du[j];
                 }
@@ -262,7 +253,7 @@ __global__ __launch_bounds__(128) void update_split_kernel(
             if (s >= 1) {
                 ForceIn<float> fi;
                 float qs[NJ], qds[NJ], v[NJ], pee[3], Rn[9];
-                handoff_read<FORCE>(&hb[(s - 1) & 1][lane], fi, qs, qds, v, pee, Rn);
+                handoff_read<FORCE>(&sh.hb[(s - 1) & 1][lane], fi, qs, qds, v, pee, Rn);
                 float l = motion_cost(M, C, tg, pee, Rn) + joint_cost(M, C, qs, qds) + torque_cost(M, C, v);
                 if constexpr (FORCE) {
                     float F[6];
@@ -278,27 +269,47 @@ __global__ __launch_bounds__(128) void update_split_kernel(
     // terminal cost phi(x_T): wave 0 hands over the final state
     if (wave == 0) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) { nb[0][j * 64 + lane] = q[j]; nb[1][j * 64 + lane] = qd[j]; }
+        for (int j = 0; j < NJ; ++j) { sh.nb[0][j * 64 + lane] = q[j]; sh.nb[1][j * 64 + lane] = qd[j]; }
     }
     __syncthreads();
-    float s_lane = INFINITY;
-    if (wave == 1) {
-        float qT[NJ], qdT[NJ], pee[3], Rn[9];
+    if (wave == 0) return INFINITY;
+    float qT[NJ], qdT[NJ], pee[3], Rn[9];
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) { qT[j] = nb[0][j * 64 + lane]; qdT[j] = nb[1][j * 64 + lane]; }
-        fk_ee(Mc, qT, pee, Rn, (float*)nullptr, (float*)nullptr);
-        Ssum += Cc.w_T * (motion_cost(Mc, Cc, tg, pee, Rn) + joint_cost(Mc, Cc, qT, qdT));
-        if (k < K) {
-            s_lane = finite_(Ssum) ? Ssum : INFINITY;
-            S[k] = s_lane;
-        }
-    }
+    for (int j = 0; j < NJ; ++j) { qT[j] = sh.nb[0][j * 64 + lane]; qdT[j] = sh.nb[1][j * 64 + lane]; }
+    fk_ee(Mc, qT, pee, Rn, (float*)nullptr, (float*)nullptr);
+    Ssum += Cc.w_T * (motion_cost(Mc, Cc, tg, pee, Rn) + joint_cost(Mc, Cc, qT, qdT));
+    return k < K && finite_(Ssum) ? Ssum : INFINITY;
+}
+
+template <typename A, bool FORCE, bool COLL>
+__global__ __launch_bounds__(128) void update_split_kernel(
+    const ModelM<float>* __restrict__ Mp, const CostM<float>* __restrict__ Cp, const double* __restrict__ q0,
+    const double* __restrict__ qd0, const double* __restrict__ target, const double* U_nom,
+    uint64_t seed, uint32_t tick, int K, int T, double lambda, float* __restrict__ noise,
+    float* __restrict__ S, int merge, int lds_noise, A* __restrict__ parts, unsigned int* __restrict__ counter,
+    double* U_new, double* __restrict__ U_shift, int* __restrict__ status)
+{
+    extern __shared__ char dyn_lds[];
+    __shared__ SplitShared sh;
+    __shared__ float Us[kMaxT * NJ];
+    __shared__ A wl[64];
+    __shared__ int last;
+    __shared__ CostM<float> Csh;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave == 0) wave_copy(&Csh, Cp, lane);
+    for (int i = threadIdx.x; i < T * NJ; i += blockDim.x) Us[i] = float(U_nom[i]);
+    const int k = blockIdx.x * 64 + lane;
+    float* tile = reinterpret_cast<float*>(dyn_lds);   // [rows][65] (noise) or [64][65] (regeneration)
+    const float s_lane = split_rollout<FORCE, COLL>(*Mp, Csh, q0, qd0, target, Us, T, K, k, seed, tick,
+                                                    (noise && k < K) ? noise + k : nullptr,
+                                                    lds_noise ? tile + lane : nullptr, sh, lane, wave);
+    if (wave == 1 && k < K) S[k] = s_lane;
     if (!merge) return;
 
     const int P = 2 + T * NJ;
     if (wave == 1) {
         wave_sync();
-        wave_partial<float, A>(s_lane, lane, T, lambda, lds_noise ? tile : nullptr, Cc, seed, tick, (uint32_t)k,
+        wave_partial<float, A>(s_lane, lane, T, lambda, lds_noise ? tile : nullptr, Csh, seed, tick, (uint32_t)k,
                                tile, wl, parts + (size_t)blockIdx.x * P);
         __threadfence();
         if (lane == 0) last = atomicAdd(counter, 1u) == gridDim.x - 1;
@@ -765,6 +776,39 @@ struct BatchProblem {
     long long part_off;   // into the partials buffer, in doubles
 };
 
+// The end of a tile on one wave: its Eq. 4 partial (noise regenerated), and
+// the merge of its problem's partials by the wave whose tile completes the
+// problem.  tr: LDS scratch [64][kLdsRowPad], wl [64].
+__device__ __forceinline__ void batch_tile_done(const BatchProblem& Pb, int2 it, float s, int lane,
+                                                const CostM<float>& C, uint64_t seed, uint32_t tick, uint32_t k,
+                                                float* tr, double* wl, double* parts, unsigned int* counters,
+                                                const double* U_nom, double* U_new, double* U_shift, int* status)
+{
+    const int T = Pb.T, P = 2 + T * NJ;
+    double* pbase = parts + Pb.part_off;
+    wave_sync();
+    if (Pb.acc64)
+        wave_partial<float, double>(s, lane, T, Pb.lambda, nullptr, C, seed, tick, k, tr, wl, pbase + (size_t)it.y * P);
+    else
+        wave_partial<float, float>(s, lane, T, Pb.lambda, nullptr, C, seed, tick, k, tr, reinterpret_cast<float*>(wl),
+                                   reinterpret_cast<float*>(pbase) + (size_t)it.y * P);
+    __threadfence();
+    const unsigned done_tiles =
+        (unsigned)__builtin_amdgcn_readfirstlane((int)atomicAdd(&counters[it.x], lane == 0 ? 1u : 0u));
+    if (done_tiles == (unsigned)(Pb.ntiles - 1)) {
+        __threadfence();
+        const double* un = U_nom + Pb.u_off;
+        double* uw = U_new + Pb.u_off;
+        double* us = U_shift ? U_shift + Pb.u_off : nullptr;
+        int* st = status ? status + it.x : nullptr;
+        if (Pb.acc64) wave_merge<double>(pbase, Pb.ntiles, T, Pb.lambda, un, uw, us, st, lane, wl);
+        else
+            wave_merge<float>(reinterpret_cast<const float*>(pbase), Pb.ntiles, T, Pb.lambda, un, uw, us, st, lane,
+                              reinterpret_cast<float*>(wl));
+        if (lane == 0) counters[it.x] = 0u;
+    }
+}
+
 // COLL: some problem of the batch has the collision term (the collision
 // rollout variants are compiled in only then).  Without it the kernel is
 // built for two resident waves per SIMD (at most 256 registers per lane,
@@ -837,31 +881,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(COLL ? 1
                 if (costs) costs[Pb.k_off + k] = s;
             }
         }
-        const int P = 2 + T * NJ;
-        double* pbase = parts + Pb.part_off;
-        wave_sync();
-        if (Pb.acc64)
-            wave_partial<float, double>(s, lane, T, Pb.lambda, nullptr, C, seed, tick, (uint32_t)k, tr[wid],
-                                        wl[wid], pbase + (size_t)it.y * P);
-        else
-            wave_partial<float, float>(s, lane, T, Pb.lambda, nullptr, C, seed, tick, (uint32_t)k, tr[wid],
-                                       reinterpret_cast<float*>(wl[wid]),
-                                       reinterpret_cast<float*>(pbase) + (size_t)it.y * P);
-        __threadfence();
-        const unsigned done_tiles =
-            (unsigned)__builtin_amdgcn_readfirstlane((int)atomicAdd(&counters[it.x], lane == 0 ? 1u : 0u));
-        if (done_tiles == (unsigned)(Pb.ntiles - 1)) {
-            __threadfence();
-            const double* un = U_nom + Pb.u_off;
-            double* uw = U_new + Pb.u_off;
-            double* us = U_shift ? U_shift + Pb.u_off : nullptr;
-            int* st = status ? status + it.x : nullptr;
-            if (Pb.acc64) wave_merge<double>(pbase, Pb.ntiles, T, Pb.lambda, un, uw, us, st, lane, wl[wid]);
-            else
-                wave_merge<float>(reinterpret_cast<const float*>(pbase), Pb.ntiles, T, Pb.lambda, un, uw, us, st,
-                                  lane, reinterpret_cast<float*>(wl[wid]));
-            if (lane == 0) counters[it.x] = 0u;
-        }
+        batch_tile_done(Pb, it, s, lane, C, seed, tick, (uint32_t)k, tr[wid], wl[wid], parts, counters, U_nom, U_new,
+                        U_shift, status);
     }
     // the last wave out resets the queue for the next launch
     __threadfence();
@@ -870,6 +891,80 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(COLL ? 1
         *queue = 0u;
         *done = 0u;
         __threadfence();
+    }
+}
+
+// The batched update with two waves per tile (split_rollout: the arithmetic
+// of batch_kernel per sample, the dynamics of a step beside the noise, force
+// estimate and cost of its neighbours), for batches of at most
+// kBatchSplitTiles tiles, one workgroup of two waves per CU: there batch_kernel
+// has at most one wave per CU and its time is one tile's chain of steps.
+// Tiles, partials, counters and the queue as in batch_kernel, at workgroup
+// granularity.  T = 18, against batch_kernel with a wave per tile: 8 tiles 130
+// us (191), 200 tiles 137 (199), 256 tiles 145 (206); past one tile per CU some
+// CU would run two in turn, 1.4 times batch_kernel's time.
+template <bool COLL>
+__global__ __launch_bounds__(128) void batch_split_kernel(
+    const BatchProblem* __restrict__ probs, const ModelM<float>* __restrict__ models,
+    const int2* __restrict__ items, int nitems, unsigned int* queue, unsigned int* done, unsigned int* counters,
+    const double* __restrict__ q, const double* __restrict__ qd, const double* __restrict__ target,
+    const double* U_nom, double* U_new, double* U_shift, float* __restrict__ costs, int* __restrict__ status,
+    const uint64_t* __restrict__ seeds, const uint64_t* __restrict__ tickp, int iter, int niter,
+    double* __restrict__ parts)
+{
+    __shared__ SplitShared sh;
+    __shared__ float Us[kMaxTBatch * NJ];
+    __shared__ float tr[64 * kLdsRowPad];
+    __shared__ double wl[64];
+    __shared__ int sItem;
+    __shared__ CostM<float> Csh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t tick = (uint32_t)(*tickp * (uint64_t)niter + (uint64_t)iter);
+    for (;;) {
+        if (tid == 0) sItem = (int)atomicAdd(queue, 1u);
+        __syncthreads();
+        const int item = __builtin_amdgcn_readfirstlane(sItem);
+        if (item >= nitems) break;
+        const int2 it = items[item];
+        const BatchProblem& Pb = probs[it.x];
+        const int T = Pb.T, K = Pb.K;
+        if (wave == 0) wave_copy(&Csh, Pb.cost, lane);
+        for (int i = tid; i < T * NJ; i += 128) Us[i] = float(U_nom[Pb.u_off + i]);
+        // problem p's model through the restrict-qualified argument at a
+        // uniform index (scalar loads), as in batch_kernel
+        const ModelM<float>& M = models[it.x];
+        const int k = it.y * 64 + lane;
+        const uint64_t seed = seeds[it.x];
+        const double* q0 = q + it.x * NJ;
+        const double* qd0 = qd + it.x * NJ;
+        const double* tgt = target + (size_t)it.x * 13;
+        float s;
+        if (COLL && Pb.coll)
+            s = Pb.force ? split_rollout<true, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, nullptr, sh,
+                                                     lane, wave)
+                         : split_rollout<false, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, nullptr,
+                                                      sh, lane, wave);
+        else
+            s = Pb.force ? split_rollout<true, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, nullptr,
+                                                      sh, lane, wave)
+                         : split_rollout<false, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, nullptr,
+                                                       sh, lane, wave);
+        if (wave == 1) {
+            if (costs && k < K) costs[Pb.k_off + k] = s;
+            batch_tile_done(Pb, it, s, lane, Csh, seed, tick, (uint32_t)k, tr, wl, parts, counters, U_nom, U_new, U_shift,
+                            status);
+        }
+        __syncthreads();
+    }
+    // the last workgroup out resets the queue for the next launch
+    if (tid == 0) {
+        __threadfence();
+        const unsigned out = atomicAdd(done, 1u);
+        if (out == gridDim.x - 1) {
+            *queue = 0u;
+            *done = 0u;
+            __threadfence();
+        }
     }
 }
 
@@ -1505,6 +1600,15 @@ template <int W, bool COLL> static hipError_t batch_t(const BatchArgs& a, int gr
     return hipGetLastError();
 }
 
+template <bool COLL> static hipError_t batch_split_t(const BatchArgs& a, int groups, hipStream_t s)
+{
+    hipLaunchKernelGGL((batch_split_kernel<COLL>), dim3(groups < a.nitems ? groups : a.nitems), dim3(128), 0, s,
+                       (const BatchProblem*)a.probs, (const ModelM<float>*)a.models, (const int2*)a.items, a.nitems,
+                       a.queue, a.done, a.counters, a.q, a.qd, a.target, a.U_nom, a.U_new, a.U_shift, a.costs,
+                       a.status, a.seeds, a.tick, a.iter, a.niter, a.parts);
+    return hipGetLastError();
+}
+
 template <bool COLL> static hipError_t batch_group_t(const BatchArgs& a, int groups, hipStream_t s)
 {
     hipLaunchKernelGGL((batch_group_kernel<COLL>), dim3(groups), dim3(64 * kBatchGroupWaves), 0, s,
@@ -1520,7 +1624,9 @@ hipError_t launch_batch(const BatchArgs& a, int waves_per_group, int groups, hip
     switch (waves_per_group) {
     case 8: return a.collision ? batch_group_t<true>(a, groups, s) : batch_group_t<false>(a, groups, s);
     case 1: return a.collision ? batch_t<1, true>(a, groups, s) : batch_t<1, false>(a, groups, s);
-    case 2: return a.collision ? batch_t<2, true>(a, groups, s) : batch_t<2, false>(a, groups, s);
+    case 2:
+        if (a.nitems <= kBatchSplitTiles) return a.collision ? batch_split_t<true>(a, groups, s) : batch_split_t<false>(a, groups, s);
+        return a.collision ? batch_t<2, true>(a, groups, s) : batch_t<2, false>(a, groups, s);
     case 4: return a.collision ? batch_t<4, true>(a, groups, s) : batch_t<4, false>(a, groups, s);
     default: return hipErrorInvalidValue;
     }

@@ -111,5 +111,6 @@ constexpr int kWeightsBlock = 256;
 constexpr int kWeightsRows = 2;
 constexpr int kMaxT = 256;
 constexpr int kMaxTBatch = 64;   // horizon limit of the batched kernel
+constexpr int kBatchSplitTiles = 256;   // batches up to this many tiles: two waves per tile
 
 }  // namespace mppi

@@ -911,6 +911,19 @@ int mppi_batch_create(const mppi_problem_desc* descs, int n, mppi_batch_t* out)
     for (int p : order)
         for (int t = 0; t < ntiles[p]; ++t) items.push_back(make_int2(p, t));
     b->nitems = (int)items.size();
+    // default launch shape: two waves per tile while every tile has a CU of
+    // its own; else one wave per tile, as many as the chip holds (two per
+    // SIMD, with the collision term one) or as there are tiles: the
+    // 64-problem batch takes 959 us on 1024 waves, 696 on 2048; 200 tiles take
+    // 231 us on 1024 waves, 199 on 200 (a workgroup without a tile still
+    // passes through the queue)
+    if (b->nitems <= kBatchSplitTiles) {
+        b->wpg = 2;
+        b->groups = b->nitems;
+    } else {
+        b->wpg = 1;
+        b->groups = std::min(b->nitems, b->collision ? 1024 : 2048);
+    }
     bool ok = hipMalloc(&b->d_raw, sizeof(mppi_robot_params) * n) == hipSuccess &&
               hipMalloc(&b->d_mf, sizeof(ModelM<float>) * n) == hipSuccess &&
               hipMalloc(&b->d_md, sizeof(ModelM<double>) * n) == hipSuccess &&

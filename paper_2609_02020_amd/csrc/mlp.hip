@@ -55,15 +55,9 @@ constexpr int kOutWaves = kMlpOutPad / 16 < kFwdWaves ? kMlpOutPad / 16 : kFwdWa
 constexpr int kOutCT = kMlpOutPad / 16 / kOutWaves;
 constexpr int kLda = 264;
 
-// FP32 -> BF16, round to nearest, ties to even (NaN stays NaN)
-__device__ __forceinline__ uint16_t to_bf16(float x)
-{
-    uint32_t u = __float_as_uint(x);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+// FP32 -> BF16, round to nearest, ties to even (NaN stays NaN): the
+// hardware's conversion
+__device__ __forceinline__ uint16_t to_bf16(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
 
 // tanh(u) = 1 - 2 / (exp(2u) + 1) with the hardware exponential and
 // reciprocal (absolute error ~1e-7, far below the BF16 rounding that
@@ -94,7 +88,18 @@ __device__ __forceinline__ v4f mfma32(v8s a, v8s b, v4f c)
                                                    0, 0);
 }
 
-constexpr int kRT = kMlpWgRows / 16;   // row tiles per workgroup
+// Rows per workgroup R: 16 (one matrix-core row tile) or, for inference of up
+// to one workgroup per CU, 4.  A row of the LDS tile then stands for 16 / R
+// equal rows of the matrix-core operand, and of a lane's four result rows
+// R / 4 are kept: row q (q < R / 4) of lane l is its result element 16 q / R,
+// row (R / 4) (l div 16) + q of the workgroup's R.  Products, and so results,
+// are those of the 16-row workgroup; what falls with R is the work per
+// element (bias, GELU, rounding, stores).  4 rows against 16: 512 rows
+// forward 5.4 us against 6.15, 1024 5.5 / 6.2, a proposal of 64 5.9 / 6.4; past
+// 1024 rows (256 workgroups) 8.4 / 6.5 at 1040.  Training gains nothing (512
+// rows 16.2 / 16.0 us): there the weights' way into the CU bounds a
+// workgroup, 656 KB at 64 bytes per cycle.
+template <int R> constexpr int kLaneRows = R / 4;
 
 // Matrix-core operand order of a BF16 matrix [N][K] read as k-contiguous
 // 16 x 32 fragments (the weights, their transposes, and the transposed
@@ -129,49 +134,56 @@ __device__ __forceinline__ void load_frag(const uint16_t* __restrict__ Bt, int n
     // issue the loads here, not next to their products
     __builtin_amdgcn_sched_barrier(0);
 }
-// acc[i][j] = sum_k A[16 i + r][k] B[16 j + c][k] over the RT row tiles of
-// the LDS tile A and the CT column tiles of f
-template <int K, int CT>
-__device__ __forceinline__ void frag_mm(const uint16_t* A, const BFrag<K, CT>& f, v4f (&acc)[kRT][CT], int lane)
+// acc[j] = sum_k A[r][k] B[16 j + c][k] over the R rows of the LDS tile A
+// and the CT column tiles of f; out[j][q]: this lane's rows of it
+template <int R, int K, int CT>
+__device__ __forceinline__ void frag_mm(const uint16_t* A, const BFrag<K, CT>& f, float (&out)[CT][kLaneRows<R>], int lane)
 {
-    const int r = lane & 15, kg = (lane >> 4) * 8;
+    const int r = (lane & 15) * R / 16, kg = (lane >> 4) * 8;
+    v4f acc[CT];
 #pragma unroll
-    for (int i = 0; i < kRT; ++i)
-#pragma unroll
-        for (int j = 0; j < CT; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int j = 0; j < CT; ++j) acc[j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int t = 0; t < K / 32; ++t) {
-        v8s a[kRT];
+        const v8s a = *reinterpret_cast<const v8s*>(A + r * kLda + 32 * t + kg);
 #pragma unroll
-        for (int i = 0; i < kRT; ++i) a[i] = *reinterpret_cast<const v8s*>(A + (16 * i + r) * kLda + 32 * t + kg);
-#pragma unroll
-        for (int i = 0; i < kRT; ++i)
-#pragma unroll
-            for (int j = 0; j < CT; ++j) acc[i][j] = mfma32(a[i], f.b[t][j], acc[i][j]);
+        for (int j = 0; j < CT; ++j) acc[j] = mfma32(a, f.b[t][j], acc[j]);
     }
+#pragma unroll
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+        for (int q = 0; q < kLaneRows<R>; ++q) out[j][q] = acc[j][16 * q / R];
 }
 
-// LDS tile columns [0, ncols) -> global [c][Bp] at rows b0..b0+15 (the
+// LDS tile columns [0, ncols) -> global [c][Bp] at rows b0..b0+R-1 (the
 // input tile only; the layers' outputs go out from their result registers)
+template <int R>
 __device__ __forceinline__ void store_transposed(const uint16_t* tile, int ncols, uint16_t* dst, int Bp, int b0,
                                                  int tid)
 {
-    for (int i = tid; i < ncols * kMlpWgRows; i += kThreads) {
-        const int c = i / kMlpWgRows, r = i % kMlpWgRows;
+    for (int i = tid; i < ncols * R; i += kThreads) {
+        const int c = i / R, r = i % R;
         dst[frag_index(c, b0 + r, Bp)] = tile[r * kLda + c];
     }
 }
 
-// One result fragment's four BF16 values (column col, rows row0 + 0..3 of
-// the workgroup's 16, row0 a multiple of 4) into the transposed global
-// buffer [feature][Bp] in operand order: the four rows are contiguous there,
-// so one 8-byte store per lane.
-__device__ __forceinline__ void store_frag_T(uint16_t* dstT, int Bp, int b0, int row0, int col, const uint16_t (&o)[4])
+// One lane's N result rows of column col (batch rows row0 + 0..N-1, row0 a
+// multiple of N) into the transposed global buffer [feature][Bp] in operand
+// order: the rows are contiguous there, so one store per lane.
+template <int N>
+__device__ __forceinline__ void store_frag_T(uint16_t* dstT, int Bp, int row0, int col, const uint16_t (&o)[N])
 {
-    uint2 v;
-    v.x = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
-    v.y = (uint32_t)o[2] | ((uint32_t)o[3] << 16);
-    *reinterpret_cast<uint2*>(dstT + frag_index(col, b0 + row0, Bp)) = v;
+    uint16_t* d = dstT + frag_index(col, row0, Bp);
+    if constexpr (N == 4) {
+        uint2 v;
+        v.x = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
+        v.y = (uint32_t)o[2] | ((uint32_t)o[3] << 16);
+        *reinterpret_cast<uint2*>(d) = v;
+    } else if constexpr (N == 2) {
+        *reinterpret_cast<uint32_t*>(d) = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
+    } else {
+        *d = o[0];
+    }
 }
 
 // this wave's bias values of a hidden layer (columns nb + 16 j + lane mod 16)
@@ -189,33 +201,31 @@ __device__ __forceinline__ void load_bias(const float* __restrict__ bias, int nb
 // reach a valid output).
 // Training (dstT non-null) also stores the activations transposed from the
 // result registers (store_frag_T).
-template <int K>
+template <int R, int K>
 __device__ __forceinline__ void hidden_forward(const uint16_t* A, const BFrag<K, kHidCT>& f, const float (&bv)[kHidCT],
-                                               float (&zo)[kRT][kHidCT][4], uint16_t* out, int rows, int w,
+                                               float (&zo)[kHidCT][kLaneRows<R>], uint16_t* out, int rows, int w,
                                                int lane, uint16_t* dstT, int Bp, int b0)
 {
-    constexpr int NC = 16 * kHidCT;
-    v4f acc[kRT][kHidCT];
-    frag_mm(A, f, acc, lane);
+    constexpr int NC = 16 * kHidCT, NE = kLaneRows<R>;
+    float acc[kHidCT][NE];
+    frag_mm<R>(A, f, acc, lane);
+    const int row0 = NE * (lane >> 4);
 #pragma unroll
-    for (int i = 0; i < kRT; ++i)
+    for (int j = 0; j < kHidCT; ++j) {
+        const int col = w * NC + 16 * j + (lane & 15);
+        uint16_t o[NE];
 #pragma unroll
-        for (int j = 0; j < kHidCT; ++j) {
-            const int col = w * NC + 16 * j + (lane & 15);
-            uint16_t o[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = 16 * i + 4 * (lane >> 4) + e;
-                const float zz = acc[i][j][e] + bv[j];
-                zo[i][j][e] = zz;
-                // 16 i + e is the wave's smallest row of this element: past
-                // `rows` no lane evaluates GELU (a uniform branch)
-                o[e] = 0;
-                if (16 * i + e < rows) o[e] = row < rows ? to_bf16(gelu_f(zz)) : (uint16_t)0;
-                out[row * kLda + col] = o[e];
-            }
-            if (dstT) store_frag_T(dstT, Bp, b0, 16 * i + 4 * (lane >> 4), col, o);
+        for (int e = 0; e < NE; ++e) {
+            const float zz = acc[j][e] + bv[j];
+            zo[j][e] = zz;
+            // e is the wave's smallest row of this element: past `rows` no
+            // lane evaluates GELU (a uniform branch)
+            o[e] = 0;
+            if (e < rows) o[e] = row0 + e < rows ? to_bf16(gelu_f(zz)) : (uint16_t)0;
+            out[(row0 + e) * kLda + col] = o[e];
         }
+        if (dstT) store_frag_T<NE>(dstT, Bp, b0 + row0, col, o);
+    }
 }
 
 // hidden layer backward: bf16((E Wt^T) * gelu'(z)) from the wave's
@@ -223,28 +233,26 @@ __device__ __forceinline__ void hidden_forward(const uint16_t* A, const BFrag<K,
 // forward pass (same fragment map), into the LDS tile out (null for the
 // first layer's signal, which no later product reads) and, transposed,
 // into dstT
-template <int K>
+template <int R, int K>
 __device__ __forceinline__ void hidden_backward(const uint16_t* E, const BFrag<K, kHidCT>& f,
-                                                const float (&zv)[kRT][kHidCT][4], uint16_t* out, int w, int lane,
+                                                const float (&zv)[kHidCT][kLaneRows<R>], uint16_t* out, int w, int lane,
                                                 uint16_t* dstT, int Bp, int b0)
 {
-    constexpr int NC = 16 * kHidCT;
-    v4f acc[kRT][kHidCT];
-    frag_mm(E, f, acc, lane);
+    constexpr int NC = 16 * kHidCT, NE = kLaneRows<R>;
+    float acc[kHidCT][NE];
+    frag_mm<R>(E, f, acc, lane);
+    const int row0 = NE * (lane >> 4);
 #pragma unroll
-    for (int i = 0; i < kRT; ++i)
+    for (int j = 0; j < kHidCT; ++j) {
+        const int col = w * NC + 16 * j + (lane & 15);
+        uint16_t o[NE];
 #pragma unroll
-        for (int j = 0; j < kHidCT; ++j) {
-            const int col = w * NC + 16 * j + (lane & 15);
-            uint16_t o[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = 16 * i + 4 * (lane >> 4) + e;
-                o[e] = to_bf16(acc[i][j][e] * gelu_d(zv[i][j][e]));
-                if (out) out[row * kLda + col] = o[e];
-            }
-            store_frag_T(dstT, Bp, b0, 16 * i + 4 * (lane >> 4), col, o);
+        for (int e = 0; e < NE; ++e) {
+            o[e] = to_bf16(acc[j][e] * gelu_d(zv[j][e]));
+            if (out) out[(row0 + e) * kLda + col] = o[e];
         }
+        store_frag_T<NE>(dstT, Bp, b0 + row0, col, o);
+    }
 }
 
 // Feature c (0..20) of state p: q / q_max, qd / qd_max, p_des, then the
@@ -277,7 +285,7 @@ __device__ __forceinline__ float feature_value(const FeatIn& f, int c)
     return (float)(f.v * sg);
 }
 
-template <bool TRAIN>
+template <bool TRAIN, int R>
 __global__ __launch_bounds__(kThreads) void mlp_forward_kernel(MlpDev d, const float* __restrict__ X, int B,
                                                                const float* __restrict__ Ytgt, float* __restrict__ Y,
                                                                double* __restrict__ U, int u_stride, float gscale,
@@ -285,10 +293,10 @@ __global__ __launch_bounds__(kThreads) void mlp_forward_kernel(MlpDev d, const f
                                                                const double* __restrict__ sqd,
                                                                const double* __restrict__ stg)
 {
-    __shared__ __align__(16) uint16_t buf[2][kMlpWgRows * kLda];
+    __shared__ __align__(16) uint16_t buf[2][R * kLda];
     __shared__ float red[kThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int b0 = blockIdx.x * kMlpWgRows;
+    const int b0 = blockIdx.x * R;
     const float* th = d.theta;
 
     const int nh = w * 16 * kHidCT;   // this wave's first column of a hidden layer
@@ -296,9 +304,9 @@ __global__ __launch_bounds__(kThreads) void mlp_forward_kernel(MlpDev d, const f
     // (one element per thread; feature columns 21..31 and rows past B are
     // zero): its loads first, then the first two layers' operands, and only
     // then the input tile's values (the loads return in order)
-    static_assert(kMlpWgRows * kMlpInPad <= kThreads, "one input element per thread");
+    static_assert(R * kMlpInPad <= kThreads, "one input element per thread");
     const int ir = tid / kMlpInPad, ic = tid % kMlpInPad;
-    const bool has_x = tid < kMlpWgRows * kMlpInPad && ic < kMlpIn && b0 + ir < B;
+    const bool has_x = tid < R * kMlpInPad && ic < kMlpIn && b0 + ir < B;
     // the element's indices clamped to a valid one, so that the loads need
     // no branch (has_x decides below whether the value is used)
     const int pr = min(b0 + ir, B - 1), pc = min(ic, kMlpIn - 1);
@@ -315,30 +323,32 @@ __global__ __launch_bounds__(kThreads) void mlp_forward_kernel(MlpDev d, const f
     load_frag(d.W2, nh, f2, lane);
     load_bias(th + kOffB2, nh, bv2, lane);
     __builtin_amdgcn_sched_barrier(0);
-    if (tid < kMlpWgRows * kMlpInPad) {
+    if (tid < R * kMlpInPad) {
         float x = 0.0f;
         if (has_x) x = (TRAIN || X) ? xv : feature_value(fin, pc);
         buf[0][ir * kLda + ic] = to_bf16(x);
     }
     __syncthreads();
-    if (TRAIN) store_transposed(buf[0], kMlpInPad, d.aT0, d.Bp, b0, tid);
+    if (TRAIN) store_transposed<R>(buf[0], kMlpInPad, d.aT0, d.Bp, b0, tid);
 
     // training keeps every row (the backward pass reads them all)
-    const int rows = TRAIN ? kMlpWgRows : min(kMlpWgRows, B - b0);
-    float z1[kRT][kHidCT][4], z2[kRT][kHidCT][4], z3[kRT][kHidCT][4];
-    hidden_forward<kMlpInPad>(buf[0], f1, bv1, z1, buf[1], rows, w, lane, TRAIN ? d.aT1 : nullptr, d.Bp, b0);
+    const int rows = TRAIN ? R : min(R, B - b0);
+    constexpr int NE = kLaneRows<R>;
+    const int row0 = NE * (lane >> 4);
+    float z1[kHidCT][NE], z2[kHidCT][NE], z3[kHidCT][NE];
+    hidden_forward<R, kMlpInPad>(buf[0], f1, bv1, z1, buf[1], rows, w, lane, TRAIN ? d.aT1 : nullptr, d.Bp, b0);
     __syncthreads();
     BFrag<kMlpHid, kHidCT> f3;
     float bv3[kHidCT];
     load_frag(d.W3, nh, f3, lane);
     load_bias(th + kOffB3, nh, bv3, lane);
-    hidden_forward<kMlpHid>(buf[1], f2, bv2, z2, buf[0], rows, w, lane, TRAIN ? d.aT2 : nullptr, d.Bp, b0);
+    hidden_forward<R, kMlpHid>(buf[1], f2, bv2, z2, buf[0], rows, w, lane, TRAIN ? d.aT2 : nullptr, d.Bp, b0);
     __syncthreads();
 
     // the output layer's operands (its 8 column tiles on the first waves)
     constexpr int NO = 16 * kOutCT;
     BFrag<kMlpHid, kOutCT> f4;
-    float b4[kOutCT], yt[kRT][kOutCT][4];
+    float b4[kOutCT], yt[kOutCT][NE];
     double us[kOutCT];   // inference into U: the torque limit of the column's joint
     if (w < kOutWaves) {
         load_frag(d.W4, w * NO, f4, lane);
@@ -348,16 +358,13 @@ __global__ __launch_bounds__(kThreads) void mlp_forward_kernel(MlpDev d, const f
             b4[j] = col < kMlpOut ? th[kOffB4 + col] : 0.0f;
             us[j] = (!TRAIN && U) ? d.scale[14 + col % 7] : 0.0;
 #pragma unroll
-            for (int i = 0; i < kRT; ++i)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int row = 16 * i + 4 * (lane >> 4) + e;
-                    yt[i][j][e] = (TRAIN && col < kMlpOut && b0 + row < B) ? Ytgt[(size_t)(b0 + row) * kMlpOut + col]
-                                                                          : 0.0f;
-                }
+            for (int e = 0; e < NE; ++e)
+                yt[j][e] = (TRAIN && col < kMlpOut && b0 + row0 + e < B)
+                               ? Ytgt[(size_t)(b0 + row0 + e) * kMlpOut + col]
+                               : 0.0f;
         }
     }
-    hidden_forward<kMlpHid>(buf[0], f3, bv3, z3, buf[1], rows, w, lane, TRAIN ? d.aT3 : nullptr, d.Bp, b0);
+    hidden_forward<R, kMlpHid>(buf[0], f3, bv3, z3, buf[1], rows, w, lane, TRAIN ? d.aT3 : nullptr, d.Bp, b0);
     __syncthreads();
 
     // output layer; training: e_4 = bf16(2 (y - y*) / (B 126)) into buf[0]
@@ -365,32 +372,30 @@ __global__ __launch_bounds__(kThreads) void mlp_forward_kernel(MlpDev d, const f
     {
         float sq = 0.0f;
         if (w < kOutWaves) {
-            v4f acc[kRT][kOutCT];
-            frag_mm(buf[1], f4, acc, lane);
+            float acc[kOutCT][NE];
+            frag_mm<R>(buf[1], f4, acc, lane);
 #pragma unroll
-            for (int i = 0; i < kRT; ++i)
+            for (int j = 0; j < kOutCT; ++j) {
+                const int col = w * NO + 16 * j + (lane & 15);
+                uint16_t o[NE];
 #pragma unroll
-                for (int j = 0; j < kOutCT; ++j) {
-                    const int col = w * NO + 16 * j + (lane & 15);
-                    uint16_t o[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int row = 16 * i + 4 * (lane >> 4) + e;
-                        const bool valid = col < kMlpOut && b0 + row < B;
-                        const float y = acc[i][j][e] + b4[j];
-                        if (!TRAIN && valid) {   // training writes neither
-                            if (Y) Y[(size_t)(b0 + row) * kMlpOut + col] = y;
-                            if (U) U[(size_t)(b0 + row) * u_stride + col] = us[j] * (double)y;
-                        }
-                        if (TRAIN) {
-                            const float res = valid ? y - yt[i][j][e] : 0.0f;
-                            sq += res * res;
-                            o[e] = to_bf16(res * gscale);
-                            buf[0][row * kLda + col] = o[e];
-                        }
+                for (int e = 0; e < NE; ++e) {
+                    const int row = row0 + e;
+                    const bool valid = col < kMlpOut && b0 + row < B;
+                    const float y = acc[j][e] + b4[j];
+                    if (!TRAIN && valid) {   // training writes neither
+                        if (Y) Y[(size_t)(b0 + row) * kMlpOut + col] = y;
+                        if (U) U[(size_t)(b0 + row) * u_stride + col] = us[j] * (double)y;
                     }
-                    if (TRAIN) store_frag_T(d.eT4, d.Bp, b0, 16 * i + 4 * (lane >> 4), col, o);
+                    if (TRAIN) {
+                        const float res = valid ? y - yt[j][e] : 0.0f;
+                        sq += res * res;
+                        o[e] = to_bf16(res * gscale);
+                        buf[0][row * kLda + col] = o[e];
+                    }
                 }
+                if (TRAIN) store_frag_T<NE>(d.eT4, d.Bp, b0 + row0, col, o);
+            }
         }
         if (!TRAIN) return;
         load_frag(d.W4t, nh, g4, lane);
@@ -408,13 +413,13 @@ __global__ __launch_bounds__(kThreads) void mlp_forward_kernel(MlpDev d, const f
 
     BFrag<kMlpHid, kHidCT> g3;
     load_frag(d.W3t, nh, g3, lane);
-    hidden_backward<kMlpOutPad>(buf[0], g4, z3, buf[1], w, lane, d.eT3, d.Bp, b0);
+    hidden_backward<R, kMlpOutPad>(buf[0], g4, z3, buf[1], w, lane, d.eT3, d.Bp, b0);
     __syncthreads();
     BFrag<kMlpHid, kHidCT> g2;
     load_frag(d.W2t, nh, g2, lane);
-    hidden_backward<kMlpHid>(buf[1], g3, z2, buf[0], w, lane, d.eT2, d.Bp, b0);
+    hidden_backward<R, kMlpHid>(buf[1], g3, z2, buf[0], w, lane, d.eT2, d.Bp, b0);
     __syncthreads();
-    hidden_backward<kMlpHid>(buf[0], g2, z1, nullptr, w, lane, d.eT1, d.Bp, b0);
+    hidden_backward<R, kMlpHid>(buf[0], g2, z1, nullptr, w, lane, d.eT1, d.Bp, b0);
 }
 
 // Adam state of one parameter, read before its gradient is known
@@ -639,6 +644,7 @@ __global__ void mlp_features_kernel(MlpDev d, int n, const double* __restrict__ 
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
+
 }  // namespace
 
 size_t mlp_scratch_bytes(int Bp)
@@ -690,17 +696,15 @@ hipError_t launch_mlp_forward(const MlpDev& d, const float* X, int B, const floa
 {
     if (B < 1 || B > d.Bp || (!X && (Ytgt || !q || !qd || !target))) return hipErrorInvalidValue;
     const float gscale = 2.0f / ((float)B * (float)kMlpOut);
-    if (Ytgt) {
-        // training covers the batch rounded up to 64 rows (padding rows carry
-        // zero inputs and zero signals; the weight gradients split that range)
-        const dim3 grid((B + kMlpRows - 1) / kMlpRows * (kMlpRows / kMlpWgRows));
-        hipLaunchKernelGGL(mlp_forward_kernel<true>, grid, dim3(kThreads), 0, s, d, X, B, Ytgt, Y, U, u_stride, gscale,
-                           q, qd, target);
-    } else {
-        const dim3 grid((B + kMlpWgRows - 1) / kMlpWgRows);
-        hipLaunchKernelGGL(mlp_forward_kernel<false>, grid, dim3(kThreads), 0, s, d, X, B, Ytgt, Y, U, u_stride,
-                           gscale, q, qd, target);
-    }
+    auto go = [&](auto kernel, int rows) {
+        hipLaunchKernelGGL(kernel, dim3(rows), dim3(kThreads), 0, s, d, X, B, Ytgt, Y, U, u_stride, gscale, q, qd,
+                           target);
+    };
+    // training covers the batch rounded up to 64 rows (padding rows carry
+    // zero inputs and zero signals; the weight gradients split that range)
+    if (Ytgt) go(mlp_forward_kernel<true, kMlpWgRows>, (B + kMlpRows - 1) / kMlpRows * (kMlpRows / kMlpWgRows));
+    else if (B <= kMlpFewRows) go(mlp_forward_kernel<false, 4>, (B + 3) / 4);
+    else go(mlp_forward_kernel<false, kMlpWgRows>, (B + kMlpWgRows - 1) / kMlpWgRows);
     return hipGetLastError();
 }
 

@@ -16,6 +16,7 @@ namespace mppi {
 constexpr int kMlpIn = 21, kMlpInPad = 32, kMlpHid = 256, kMlpOut = 126, kMlpOutPad = 128;
 constexpr int kMlpRows = 64;      // batch granularity: training buffers and batches padded to it
 constexpr int kMlpWgRows = 16;    // states per forward workgroup (one matrix-core row tile)
+constexpr int kMlpFewRows = 1024; // inference up to this many rows: 4 per workgroup (mlp.hip)
 constexpr int kOffW1 = 0;
 constexpr int kOffB1 = kOffW1 + kMlpHid * kMlpIn;
 constexpr int kOffW2 = kOffB1 + kMlpHid;

@@ -209,14 +209,21 @@ def _dp(a):
     return a.ctypes.data_as(C.POINTER(C.c_double))
 
 
+_dtypes: dict = {}
+
+
 def _dev(t, dtype: str, n: int, name: str):
     """Device pointer of a torch tensor that a kernel reads or writes n
     elements of, after checking what the C ABI cannot check on a raw
     pointer: a CUDA (HIP) tensor, contiguous, of the element type the
     kernels use, with at least n elements.  None passes through (the
-    library decides whether the argument is optional)."""
+    library decides whether the argument is optional).  The smallest calls
+    take as long as their host work, so an accepted tensor passes one test."""
     if t is None:
         return None
+    if (getattr(t, "is_cuda", False) and dtype in _dtypes and t.dtype is _dtypes[dtype] and t.numel() >= n
+            and t.is_contiguous()):
+        return t.data_ptr()
     import torch
     if not getattr(t, "is_cuda", False):
         raise ValueError("%s must be a device tensor" % name)
@@ -226,13 +233,12 @@ def _dev(t, dtype: str, n: int, name: str):
         raise ValueError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if t.numel() < n:
         raise ValueError("%s needs %d elements, got %d" % (name, n, t.numel()))
-    return C.c_void_p(t.data_ptr())
+    _dtypes[dtype] = getattr(torch, dtype)
+    return t.data_ptr()
 
 
 def _stream_ptr(stream):
-    if stream is None:
-        return None
-    return C.c_void_p(int(stream.cuda_stream))
+    return None if stream is None else int(stream.cuda_stream)
 
 
 def _device_io(io: dict, K: int, T: int, precision: int) -> DeviceIO:
@@ -241,13 +247,18 @@ def _device_io(io: dict, K: int, T: int, precision: int) -> DeviceIO:
     d = DeviceIO()
     rdt = "float64" if precision == FP64 else "float32"
     TJ = T * NJ
-    spec = {"q": ("float64", NJ), "qd": ("float64", NJ), "target": ("float64", 13),
-            "U_nominal": ("float64", TJ), "U_new": ("float64", TJ), "U_shift": ("float64", TJ),
-            "costs": (rdt, K), "noise": (rdt, TJ * K), "status": ("int32", 1)}
-    for key, (dt, n) in spec.items():
-        setattr(d, key, _dev(io.get(key), dt, n, key))
-    d.seed = int(io.get("seed", 0))
-    d.tick = int(io.get("tick", 0))
+    get = io.get
+    d.q = _dev(get("q"), "float64", NJ, "q")
+    d.qd = _dev(get("qd"), "float64", NJ, "qd")
+    d.target = _dev(get("target"), "float64", 13, "target")
+    d.U_nominal = _dev(get("U_nominal"), "float64", TJ, "U_nominal")
+    d.U_new = _dev(get("U_new"), "float64", TJ, "U_new")
+    d.U_shift = _dev(get("U_shift"), "float64", TJ, "U_shift")
+    d.costs = _dev(get("costs"), rdt, K, "costs")
+    d.noise = _dev(get("noise"), rdt, TJ * K, "noise")
+    d.status = _dev(get("status"), "int32", 1, "status")
+    d.seed = int(get("seed", 0))
+    d.tick = int(get("tick", 0))
     return d
 
 

@@ -120,8 +120,15 @@ MPPI_HD float rsqrt_sqrt_(float x)
 #endif
 }
 MPPI_HD double rsqrt_sqrt_(double x) { return std::sqrt(x); }
-// 1 / sqrt(x)
-MPPI_HD float rsqrt_(float x) { return rcp_(rsqrt_sqrt_(x)); }
+// 1 / sqrt(x): in FP32 the hardware's (1 ulp)
+MPPI_HD float rsqrt_(float x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_rsqf(x);
+#else
+    return 1.0f / std::sqrt(x);
+#endif
+}
 MPPI_HD double rsqrt_(double x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)

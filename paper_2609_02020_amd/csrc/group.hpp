@@ -15,8 +15,8 @@
 //                V_j = sum_{i<=j} S_i qd_i and velocity-product
 //                accelerations prefix sums of V_i x S_i qd_i (gravity as
 //                the base acceleration);
-//   bias forces  f_j = I_j A_j + V_j x* I_j V_j (Newton-Euler per link,
-//                lane 7 carries the negated wall wrench) and suffix sums
+//   bias forces  f_j = I_j A_j + V_j x* I_j V_j (Newton-Euler per link, at
+//                its CoM; lane 7 carries the negated wall wrench) and suffix sums
 //                give h_j = S_j . sum_{i>=j} f_i, i.e. h(q, qd) of Eq. 5
 //                less the external torque;
 //   inertia      composite-rigid-body inertias Ic_j = sum_{i>=j} I_i
@@ -32,12 +32,16 @@
 //                where the estimate is taken) and M = L D L^T:
 //                lane r (r < 6) solves L y = (row r of J)^T, lane 6
 //                L y = tau_F, and D^-1/2 y is column j of [A^T | y'] with
-//                J M^-1 J^T = A A^T and J M^-1 tau_F = A y'; the wrench is
-//                the least-squares solution of A^T x = y' by modified
-//                Gram-Schmidt with column j in lane j (six broadcast
-//                steps) and a back substitution in every lane -- without
-//                forming J M^-1 J^T, whose condition number (the square of
-//                A's) exceeds 1 / u32 near kinematic singularities;
+//                J M^-1 J^T = A A^T and J M^-1 tau_F = A y'; transposed
+//                through LDS, so that lane j holds joint j's row, the
+//                least-squares solution of A^T x = y' by modified
+//                Gram-Schmidt takes its products as sums over the group
+//                (three DPP adds each; 19 % fewer instructions of the cost
+//                part than with column j in lane j and the pivot column
+//                broadcast) and ends in a back substitution in every lane
+//                -- without forming J M^-1 J^T, whose condition number (the
+//                square of A's) exceeds 1 / u32 near kinematic
+//                singularities;
 //   cost         lane 7 adds the pose and force terms of Eqs. 9-13, lanes
 //                0..6 their joint's limit and torque terms (Eq. 14), and
 //                the collision pairs of Eq. 15 are dealt over the eight
@@ -47,7 +51,8 @@
 // cross-lane moves (shr<D>: value of lane j - D, 0 for j < D; shr_one<D>:
 // the same with 1 for j < D; add_shr<D> /
 // add_shl<D>: x plus the value of lane j - D / j + D, plus 0 where there
-// is none; bcast<K>: of lane K), sum (over the group), sync() (orders the
+// is none; bcast<K>: of lane K), sum (over the group, the same bits in every
+// lane), sync() (orders the
 // group's LDS area) and shm (that area, kGxCount values).  On the device G
 // is eight lanes of a row of 16, two groups interleaved (joint j in lane
 // 2 j + p), so that DPP row shifts by 2 D stay within a group and fill the
@@ -67,11 +72,10 @@ constexpr int kGroup = 8;
 // one of the rest, which only the dynamics part touches.
 constexpr int kGxSF = 0;                   // [8][6]: S_j
 constexpr int kGxTf = kGxSF + 8 * 6;       // [8]: tau_F
-constexpr int kGxH = kGxTf + 8;            // [8][12]: handoff to the cost part: q, qd, v, p_j, h_c, m_c
+constexpr int kGxH = kGxTf + 8;            // [8][12]: handoff to the cost part: p_j, q, qd, v, h_c, m_c
                                            // (lanes 0..6); lane 7: p_ee, R_ee
 constexpr int kGxOm = kGxH + 8 * 12;       // [8][8]: the LDL^T factor of M (row i: L below the diagonal,
-                                           // 1 / d_i on it), then lane j's column of the force solve's
-                                           // triangular factor
+                                           // 1 / d_i on it), then L^-1 [J^T | tau_F] (row i: joint i)
 constexpr int kGxPart = kGxOm + 8 * 8;     // 216
 constexpr int kGxRow = kGxPart;            // [8][8]: M row j up to the diagonal
 constexpr int kGxRhs = kGxRow + 8 * 8;     // [8]: tau - h
@@ -237,27 +241,25 @@ template <typename R> MPPI_HD R group_force_cost(const GroupCostW<R>& W, const T
     return s;
 }
 
-// One modified Gram-Schmidt step of lsq_wrench on the group: column S of
-// [A^T | y] (lane S) is broadcast; every lane takes its entry of row S of
-// the triangular factor, Rc[S] = q_S . col (q_S the normalised column S),
-// and lanes j > S remove the q_S component from their column.  idg[S] =
-// 1 / |column S| in every lane.
-template <int S, typename R, class G> MPPI_HD void group_mgs_step(const G& g, R* col, R* Rc, R* idg)
+// One modified Gram-Schmidt step of lsq_wrench on the group with joint j's
+// row of [A^T | y] in lane j (a[0..5], a[6] = y): the products of column S
+// with itself and the later columns are sums over the group, which every
+// lane gets, so row S of the triangular factor (Rm[S][c] = q_S . column c,
+// Rm[S][6] = q_S . y, q_S the normalised column S) and idg = 1 / |column S|
+// end in every lane's registers, and each lane removes the q_S component
+// from its entries.
+template <int S, typename R, class G> MPPI_HD void group_mgs_step(const G& g, R* a, R (&Rm)[6][NJ], R* idg)
 {
-    R u[NJ];
+    R p[NJ];
 #pragma unroll
-    for (int i = 0; i < NJ; ++i) u[i] = g.template bcast<S>(col[i]);
-    R n2 = R(0), d = R(0);
+    for (int c = S; c < NJ; ++c) p[c] = g.sum(a[S] * a[c]);
+    const R id = rsqrt_(p[S]);
+    idg[S] = id;
 #pragma unroll
-    for (int i = 0; i < NJ; ++i) {
-        n2 = fma_(u[i], u[i], n2);
-        d = fma_(u[i], col[i], d);
+    for (int c = S + 1; c < NJ; ++c) {
+        Rm[S][c] = p[c] * id;
+        a[c] = fma_(-(Rm[S][c] * id), a[S], a[c]);
     }
-    idg[S] = rsqrt_(n2);
-    Rc[S] = d * idg[S];
-    const R coef = g.j > S ? d * idg[S] * idg[S] : R(0);
-#pragma unroll
-    for (int i = 0; i < NJ; ++i) col[i] = fma_(-coef, u[i], col[i]);
 }
 
 // What a group step leaves for inspection (host checks): lane 7's EE pose,
@@ -341,7 +343,26 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
     // x z_j is also the EE Jacobian's linear column about the EE point
     R z[3] = {Q[2] * L.live, Q[5] * L.live, Q[8] * L.live}, pz[3];
     cross3(pr, z, pz);
-    // link inertia about O: mass m, first moment h = m c, rotational I_O
+    // gather S: in FP32 every lane requests all seven slots here, long before
+    // the rows of M need them, so that the exchange's round trip overlaps
+    // the bias forces and subtree sums; in FP64 the 84 registers would spill
+    // (K = 16384, T = 36: 404 us against 330), and they are read with the rows
+    R* slot = X + kGxSF + j * 6;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) { slot[a] = z[a]; slot[3 + a] = pz[a]; }
+    g.sync();
+    constexpr bool early = sizeof(R) == 4;
+    R Sc[NJ][6];
+    auto gather = [&] {
+#pragma unroll
+        for (int c = 0; c < NJ; ++c)
+#pragma unroll
+            for (int a = 0; a < 6; ++a) Sc[c][a] = X[kGxSF + c * 6 + a];
+        sched_fence();   // in one round trip
+    };
+    if (early) gather();
+    // CoM about O, rotational inertia about the CoM in world axes; link
+    // inertia about O: mass m, first moment h = m c, rotational I_O
     R cw[3], Ib[6];
     mv3(Q, L.com, cw);
     cw[0] += pr[0]; cw[1] += pr[1]; cw[2] += pr[2];
@@ -376,29 +397,29 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
     prefix_sum<6>(g, A);
     A[3] -= grav[0]; A[4] -= grav[1]; A[5] -= grav[2];
 
-    // ---- link forces f = I A + V x* (I V)
-    auto inertia_mul = [&](const R* P, const R* x, R* y) {
-        // (I_O w + h x v, m v - h x w)
-        R hv[3], hw[3];
-        cross3(P, x + 3, hv);
-        cross3(P, x, hw);
-        y[0] = P[4] * x[0] + P[7] * x[1] + P[8] * x[2] + hv[0];
-        y[1] = P[7] * x[0] + P[5] * x[1] + P[9] * x[2] + hv[1];
-        y[2] = P[8] * x[0] + P[9] * x[1] + P[6] * x[2] + hv[2];
-        y[3] = P[3] * x[3] - hw[0];
-        y[4] = P[3] * x[4] - hw[1];
-        y[5] = P[3] * x[5] - hw[2];
-    };
+    // ---- link forces about O, by Newton and Euler at the CoM: with its
+    // velocity v_c = v + w x c and acceleration a_c = a + al x c + w x v_c,
+    // F = m a_c and N = Ib al + w x (Ib w), then (N + c x F, F) -- a third
+    // fewer operations than I A + V x* (I V) with the inertia about O
     R f[6];
     {
-        R IV[6], t1[3], t2[3], t3[3];
-        inertia_mul(In, A, f);
-        inertia_mul(In, V, IV);
-        cross3(V, IV, t1);
-        cross3(V + 3, IV + 3, t2);
-        cross3(V, IV + 3, t3);
-        f[0] += t1[0] + t2[0]; f[1] += t1[1] + t2[1]; f[2] += t1[2] + t2[2];
-        f[3] += t3[0]; f[4] += t3[1]; f[5] += t3[2];
+        auto sym_mul = [](const R* I, const R* x, R* y) {
+            y[0] = I[0] * x[0] + I[3] * x[1] + I[4] * x[2];
+            y[1] = I[3] * x[0] + I[1] * x[1] + I[5] * x[2];
+            y[2] = I[4] * x[0] + I[5] * x[1] + I[2] * x[2];
+        };
+        R t1[3], t2[3], vc[3], ac[3], Iw[3], Ia[3];
+        cross3(V, cw, t1);
+        vc[0] = V[3] + t1[0]; vc[1] = V[4] + t1[1]; vc[2] = V[5] + t1[2];
+        cross3(A, cw, t1);
+        cross3(V, vc, t2);
+        ac[0] = A[3] + t1[0] + t2[0]; ac[1] = A[4] + t1[1] + t2[1]; ac[2] = A[5] + t1[2] + t2[2];
+        f[3] = L.m * ac[0]; f[4] = L.m * ac[1]; f[5] = L.m * ac[2];
+        sym_mul(Ib, V, Iw);
+        sym_mul(Ib, A, Ia);
+        cross3(V, Iw, t1);
+        cross3(cw, f + 3, t2);
+        f[0] = Ia[0] + t1[0] + t2[0]; f[1] = Ia[1] + t1[1] + t2[1]; f[2] = Ia[2] + t1[2] + t2[2];
     }
     if (ext == EXTW_WALL) {
         // unilateral spring-damper at the EE point (lane 7's frame origin,
@@ -420,17 +441,19 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
     suffix_sum<6>(g, f);
     suffix_sum<10>(g, In);
     const R hq = dot3(z, f) + dot3(pz, f + 3);
-    // Ic S and the gravity torque S . Ic (0, -g)
+    // Ic S: (I_O w + h x v, m v - h x w) of the subtree
     R Fm[6];
     {
-        R Sv[6] = {z[0], z[1], z[2], pz[0], pz[1], pz[2]};
-        inertia_mul(In, Sv, Fm);
+        R hv[3], hw[3];
+        cross3(In, pz, hv);
+        cross3(In, z, hw);
+        Fm[0] = In[4] * z[0] + In[7] * z[1] + In[8] * z[2] + hv[0];
+        Fm[1] = In[7] * z[0] + In[5] * z[1] + In[9] * z[2] + hv[1];
+        Fm[2] = In[8] * z[0] + In[9] * z[1] + In[6] * z[2] + hv[2];
+        Fm[3] = In[3] * pz[0] - hw[0];
+        Fm[4] = In[3] * pz[1] - hw[1];
+        Fm[5] = In[3] * pz[2] - hw[2];
     }
-
-    // ---- gather S (Ic S stays in this lane)
-    R* slot = X + kGxSF + j * 6;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) { slot[a] = z[a]; slot[3 + a] = pz[a]; }
     if (FORCE && FDYN) {
         // tau_F (less the gravity torque S . Ic (0, -g) when force_mode is 0)
         R tf = v;
@@ -442,22 +465,18 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
         }
         X[kGxTf + j] = ee ? R(0) : tf;
     }
-    g.sync();
+    if (!early) gather();
     // row j of M up to the diagonal: M_jc = S_c . (Ic S)_j (c <= j), plus
-    // the armature; every lane reads the slots at the same offsets and
-    // multiplies by its own Ic S.  Above the diagonal, and in the EE lane,
-    // the same products are not M (nothing reads that part of the rows).
-    R Sc[NJ][6], row[NJ];
-#pragma unroll
-    for (int c = 0; c < NJ; ++c)
-#pragma unroll
-        for (int a = 0; a < 6; ++a) Sc[c][a] = X[kGxSF + c * 6 + a];
-    sched_fence();   // the 42 reads in one round trip
+    // the armature; every lane holds all the S_c and multiplies by its own
+    // Ic S.  Above the diagonal, and in the EE lane, the same products are
+    // not M (nothing reads that part of the rows).
+    R row[NJ];
 #pragma unroll
     for (int c = 0; c < NJ; ++c) {
-        const R* S = Sc[c];
-        R s = S[0] * Fm[0] + S[1] * Fm[1] + S[2] * Fm[2] + S[3] * Fm[3] + S[4] * Fm[4] + S[5] * Fm[5];
-        row[c] = s + (c == j ? L.arm : R(0));
+        R s = c == j ? L.arm : R(0);
+#pragma unroll
+        for (int a = 0; a < 6; ++a) s = fma_(Sc[c][a], Fm[a], s);
+        row[c] = s;
     }
 #pragma unroll
     for (int c = 0; c < NJ; ++c) rows[j * 8 + c] = row[c];
@@ -475,10 +494,11 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
     // behind these writes
     R* h = X + kGxH + j * 12;
     {
-        const R own[12] = {q, qd, v, p[0], p[1], p[2], In[0], In[1], In[2], In[3], R(0), R(0)};
-        const R eep[12] = {p[0], p[1], p[2], Q[0], Q[1], Q[2], Q[3], Q[4], Q[5], Q[6], Q[7], Q[8]};
+        const R own[9] = {q, qd, v, In[0], In[1], In[2], In[3], Q[7], Q[8]};   // the last two: no one's
 #pragma unroll
-        for (int a = 0; a < 12; ++a) h[a] = ee ? eep[a] : own[a];
+        for (int a = 0; a < 3; ++a) h[a] = p[a];
+#pragma unroll
+        for (int a = 0; a < 9; ++a) h[3 + a] = ee ? Q[a] : own[a];
     }
 #pragma unroll
     for (int i = 0; i < NJ; ++i) {
@@ -537,8 +557,8 @@ MPPI_HD R group_cost(const G& g, const GroupLink<R>& L, const CostM<R>& C, const
         // obstacle s - 7
         auto ends = [&](int sid, R* e0, R* e1) {
             if (sid < NJ) {
-                const R* a = X + kGxH + sid * 12 + 3;
-                const R* b = X + kGxH + (sid + 1) * 12 + (sid + 1 < NJ ? 3 : 0);
+                const R* a = X + kGxH + sid * 12;
+                const R* b = X + kGxH + (sid + 1) * 12;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) { e0[c] = a[c]; e1[c] = b[c]; }
             } else {
@@ -594,9 +614,17 @@ MPPI_HD R group_cost(const G& g, const GroupLink<R>& L, const CostM<R>& C, const
         R bF[NJ];
 #pragma unroll
         for (int i = 0; i < NJ; ++i) bF[i] = X[kGxTf + i];
-        // ---- lane r < 6 solves for row r of J, lane 6 (and 7) for tau_F;
-        // scaled by D^-1/2 that is column j of [A^T | y] with Omega = A A^T
-        // and J M^-1 tau_F = A y (M = L D L^T, A^T = D^-1/2 L^-1 J^T)
+        // 1 / d of this lane's joint (lane 7: of joint 6, weighted 0 below)
+        const int jr = j < NJ ? j : NJ - 1;
+        R idj = Fc.id[0];
+        if (!fac && HANDOFF) {
+            idj = X[kGxOm + jr * 8 + jr];
+        } else {
+#pragma unroll
+            for (int i = 1; i < NJ; ++i) idj = jr == i ? Fc.id[i] : idj;
+        }
+        // ---- lane r < 6 solves for row r of J, lane 6 (and 7) for tau_F:
+        // with M = L D L^T, column j of L^-1 [J^T | tau_F]
         R col[NJ];
 #pragma unroll
         for (int i = 0; i < NJ; ++i) {
@@ -605,36 +633,32 @@ MPPI_HD R group_cost(const G& g, const GroupLink<R>& L, const CostM<R>& C, const
             for (int c = 0; c < i; ++c) s = fma_(-Fc.Lm[i][c], col[c], s);
             col[i] = s;
         }
-#pragma unroll
-        for (int i = 0; i < NJ; ++i) col[i] *= rsqrt_sqrt_(Fc.id[i]);
-        // least squares A^T x = y by modified Gram-Schmidt over the lanes
-        // (lsq_wrench's arithmetic with column j in lane j): this lane's
-        // column of the triangular factor (Rc[s], s < j; lane 6: Q^T y)
-        R Rc[6], idg[6];
-        group_mgs_step<0>(g, col, Rc, idg);
-        group_mgs_step<1>(g, col, Rc, idg);
-        group_mgs_step<2>(g, col, Rc, idg);
-        group_mgs_step<3>(g, col, Rc, idg);
-        group_mgs_step<4>(g, col, Rc, idg);
-        group_mgs_step<5>(g, col, Rc, idg);
-#pragma unroll
-        for (int s = 0; s < 6; ++s) X[kGxOm + j * 8 + s] = Rc[s];
+        // transposed through the group's area: joint j's row in lane j,
+        // scaled by D^-1/2 a row of [A^T | y] with Omega = A A^T and
+        // J M^-1 tau_F = A y (A^T = D^-1/2 L^-1 J^T)
         g.sync();
-        // x = Rm^-1 Q^T y in every lane: (moment, force) about p_ee; the
-        // triangle and Q^T y are read in one round trip
-        R Rm[6][6], qy[6], bb[6];
 #pragma unroll
-        for (int s = 0; s < 6; ++s) {
-            qy[s] = X[kGxOm + 6 * 8 + s];
+        for (int i = 0; i < NJ; ++i) X[kGxOm + i * 8 + j] = col[i];
+        g.sync();
+        R a[NJ];
+        const R sD = rsqrt_sqrt_(idj) * L.live;
 #pragma unroll
-            for (int c = s + 1; c < 6; ++c) Rm[c][s] = X[kGxOm + c * 8 + s];
-        }
-        sched_fence();
+        for (int c = 0; c < NJ; ++c) a[c] = X[kGxOm + jr * 8 + c] * sD;
+        // least squares A^T x = y by modified Gram-Schmidt over the lanes
+        // (lsq_wrench's factorisation)
+        R Rm[6][NJ], idg[6], bb[6];
+        group_mgs_step<0>(g, a, Rm, idg);
+        group_mgs_step<1>(g, a, Rm, idg);
+        group_mgs_step<2>(g, a, Rm, idg);
+        group_mgs_step<3>(g, a, Rm, idg);
+        group_mgs_step<4>(g, a, Rm, idg);
+        group_mgs_step<5>(g, a, Rm, idg);
+        // x = Rm^-1 Q^T y in every lane: (moment, force) about p_ee
 #pragma unroll
         for (int s = 5; s >= 0; --s) {
-            R t = qy[s];
+            R t = Rm[s][6];
 #pragma unroll
-            for (int c = s + 1; c < 6; ++c) t = fma_(-Rm[c][s], bb[c], t);
+            for (int c = s + 1; c < 6; ++c) t = fma_(-Rm[s][c], bb[c], t);
             bb[s] = t * idg[s];
         }
         const R F[6] = {bb[3], bb[4], bb[5], bb[0], bb[1], bb[2]};

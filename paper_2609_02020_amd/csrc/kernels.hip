@@ -400,18 +400,13 @@ template <typename R> struct DevGroup {
         }
         return t;
     }
-    // over the group: joints j ^ 1, ^ 2, ^ 4 are lanes ^ 2, ^ 4, ^ 8, each
-    // reached by DPP within the row (a quad permutation, then pairs of
-    // bank-masked row shifts by 4 and by 8)
+    // over the group, the same bits in every lane: rotations of the row by
+    // 8, 4 and 2 lanes stay within a sample, each in FP32 one DPP add
     __device__ R sum(R x) const
     {
-        x += dpp<0x4E, 0xF, 0xF, true>(R(0), x);   // [2,3,0,1]
-        R t = dpp<0x104, 0xF, 0x5, false>(R(0), x);   // banks 0, 2 <- +4
-        t = dpp<0x114, 0xF, 0xA, false>(t, x);        // banks 1, 3 <- -4
-        x += t;
-        t = dpp<0x108, 0xF, 0x3, false>(R(0), x);     // banks 0, 1 <- +8
-        t = dpp<0x118, 0xF, 0xC, false>(t, x);        // banks 2, 3 <- -8
-        return x + t;
+        x += dpp<0x128, 0xF, 0xF, true>(R(0), x);
+        x += dpp<0x124, 0xF, 0xF, true>(R(0), x);
+        return x + dpp<0x122, 0xF, 0xF, true>(R(0), x);
     }
     __device__ void sync() const { wave_sync(); }
 };
@@ -496,7 +491,7 @@ __device__ __forceinline__ R group_cost_loop(const ModelM<R>& M, const CostM<R>&
             for (int a = 0; a < 3; ++a) pe[a] = h[a];
 #pragma unroll
             for (int a = 0; a < 9; ++a) Re[a] = h[3 + a];
-            Sl += group_cost<R, FORCE, COLL, DevGroup<R>, COLL, true>(g, L, C, W, tg, grav, Xs, nullptr, h[0], h[1], h[2],
+            Sl += group_cost<R, FORCE, COLL, DevGroup<R>, COLL, true>(g, L, C, W, tg, grav, Xs, nullptr, h[3], h[4], h[5],
                                                                       pe, Re);
         }
         __syncthreads();

@@ -176,7 +176,7 @@ int mppi_set_cost(mppi_handle_t h, const mppi_cost_params* cost);
  * wave per 64 samples (the same arithmetic per sample as 2).  8 gives
  * every sample eight lanes of a wave, one per joint and one for the EE
  * frame (the default; rollouts of the articulated-body route, elsewhere,
- * and in FP64 for 36864 < K <= 49152, it acts as 2): kinematics, twists and bias
+ * and in FP64 for 40960 < K <= 49152, it acts as 2): kinematics, twists and bias
  * forces by scans over the lanes, the inertia of Eq. 8 from
  * composite-rigid-body inertias, Eq. 6 by an LDL^T solve, the force
  * estimate of Eq. 13 with its right-hand sides split over the lanes and

@@ -255,10 +255,11 @@ template <int S, typename R, class G> MPPI_HD void group_mgs_step(const G& g, R*
     for (int c = S; c < NJ; ++c) p[c] = g.sum(a[S] * a[c]);
     const R id = rsqrt_(p[S]);
     idg[S] = id;
+    const R q = a[S] * id;
 #pragma unroll
     for (int c = S + 1; c < NJ; ++c) {
         Rm[S][c] = p[c] * id;
-        a[c] = fma_(-(Rm[S][c] * id), a[S], a[c]);
+        a[c] = fma_(-Rm[S][c], q, a[c]);
     }
 }
 
@@ -531,16 +532,60 @@ MPPI_HD R group_dynamics(const G& g, const GroupLink<R>& L, const CostM<R>& C, c
     return qj;
 }
 
+// The collision term of Eqs. 14-15: pair i belongs to lane i mod 8 and to
+// round i / 8; a lane keeps its pairs of up to four rounds.  A pair past
+// n_pairs has a threshold of 0 and never hits.
+constexpr int kGxRounds = 32 / kGroup;
+template <typename R> struct GroupPairs {
+    int a[kGxRounds], b[kGxRounds];   // segments: link s from p_s to p_s+1 (p_7 = p_ee), or obstacle s - 7
+    R d2[kGxRounds];                  // squared thresholds
+    int rounds;                       // the same in every lane
+};
+
+template <typename R> MPPI_HD void group_pairs(const CostM<R>& C, int j, GroupPairs<R>& P)
+{
+#pragma unroll
+    for (int r = 0; r < kGxRounds; ++r) {
+        P.a[r] = C.pa[r * kGroup + j];
+        P.b[r] = C.pb[r * kGroup + j];
+        P.d2[r] = C.dth2[r * kGroup + j];
+    }
+    P.rounds = uniform_((C.n_pairs + kGroup - 1) / kGroup);
+}
+
+// This lane's hits among its pairs of rounds FIRST, FIRST + STEP, ..., from
+// the joint origins and the EE point in the handoff.  A segment's ends are
+// read at a selected address, not in a branch per kind of segment: lanes of
+// one wave hold both kinds (a wave ran the four cases of a pair one after
+// another).  With this and the rounds dealt over both waves of a pair of
+// waves, K = 4096, T = 18 with 20 pairs takes 44.3 us (56.8 with all rounds
+// on the cost wave and the branches; 47.5 with the first and third round on
+// the dynamics wave instead of the second); FP64 79 us (94).
+template <int FIRST, int STEP, typename R>
+MPPI_HD R group_hits(const GroupPairs<R>& P, const CostM<R>& C, const R* X)
+{
+    R hits = R(0);
+#pragma unroll
+    for (int r = FIRST; r < kGxRounds; r += STEP) {
+        if (r >= P.rounds) break;
+        const bool la = P.a[r] < NJ, lb = P.b[r] < NJ;
+        const R* a0 = la ? X + kGxH + P.a[r] * 12 : C.obs[P.a[r] - NJ];
+        const R* b0 = lb ? X + kGxH + P.b[r] * 12 : C.obs[P.b[r] - NJ];
+        const R* a1 = a0 + (la ? 12 : 3);
+        const R* b1 = b0 + (lb ? 12 : 3);
+        hits += seg_dist2(a0, a1, b0, b1) < P.d2[r] ? R(1) : R(0);
+    }
+    return hits;
+}
+
 // Cost part of one step: the force estimate of Eq. 13 (FORCE) from the
 // factor of M (fac; when null, the one group_dynamics left in X with
 // HANDOFF, else M's rows in X factorised again) and the Jacobian rows left
 // in X, and this lane's running cost at (x_t, v_t): pose and
 // force terms in lane 7 (pee, Re: its EE pose), joint-limit and torque
-// terms in lanes 0..6, and with COLL the collision term of Eqs. 14-15 with
-// the pairs dealt over the lanes (pair i to lane i mod 8; link segments
-// from the joint origins and the EE point in the handoff).  Uses the kGxOm
+// terms in lanes 0..6 (the collision term is group_hits').  Uses the kGxOm
 // part of X.
-template <typename R, bool FORCE, bool COLL, class G, bool FDYN = false, bool HANDOFF = false>
+template <typename R, bool FORCE, class G, bool FDYN = false, bool HANDOFF = false>
 MPPI_HD R group_cost(const G& g, const GroupLink<R>& L, const CostM<R>& C, const GroupCostW<R>& W,
                      const TargetM<R>& tg, const R* grav, R* X, const GroupFactor<R>* fac, R q, R qd, R v,
                      const R* pee, const R* Re, R* Fout = nullptr)
@@ -552,30 +597,6 @@ MPPI_HD R group_cost(const G& g, const GroupLink<R>& L, const CostM<R>& C, const
     for (int a = 0; a < 6; ++a) sj[a] = X[kGxSF + j * 6 + a];
     sched_fence();   // with the handoff reads: one round trip
     R ell = R(0);
-    if (COLL) {
-        // segment id s: link s from P[s] to P[s + 1] (P[7] = EE point), or
-        // obstacle s - 7
-        auto ends = [&](int sid, R* e0, R* e1) {
-            if (sid < NJ) {
-                const R* a = X + kGxH + sid * 12;
-                const R* b = X + kGxH + (sid + 1) * 12;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) { e0[c] = a[c]; e1[c] = b[c]; }
-            } else {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) { e0[c] = C.obs[sid - NJ][c]; e1[c] = C.obs[sid - NJ][3 + c]; }
-            }
-        };
-        R hits = R(0);
-        g.sync();   // the other lanes' handoff (written at the end of the dynamics part)
-        for (int i = j; i < C.n_pairs; i += kGroup) {
-            R a0[3], a1[3], b0[3], b1[3];
-            ends(C.pa[i], a0, a1);
-            ends(C.pb[i], b0, b1);
-            if (seg_dist2(a0, a1, b0, b1) < C.dth2[i]) hits += R(1);
-        }
-        ell += C.w_coll * hits;
-    }
     if (FORCE) {
         // tau_F of this lane's joint: v, less the gravity torque
         // S . Ic (0, -g) of the subtree when force_mode is 0
@@ -685,7 +706,13 @@ MPPI_HD R group_step(const G& g, const GroupLink<R>& L, const CostM<R>& C, const
     qdd = group_dynamics<R, FORCE, G, COLL>(g, L, C, grav, ext, q, qd, tau, v, g.shm, &fac, p, Q);
     GroupCostW<R> W;
     group_cost_w(C, W);
-    const R ell = group_cost<R, FORCE, COLL, G, COLL>(g, L, C, W, tg, grav, g.shm, &fac, q, qd, v, p, Q, F);
+    R ell = group_cost<R, FORCE, G, COLL>(g, L, C, W, tg, grav, g.shm, &fac, q, qd, v, p, Q, F);
+    if (COLL) {
+        g.sync();   // the other lanes' handoff
+        GroupPairs<R> gp;
+        group_pairs(C, g.j, gp);
+        ell += C.w_coll * group_hits<0, 1>(gp, C, g.shm);
+    }
     if (dbg) {
         dbg->qdd = qdd;
 #pragma unroll
@@ -729,6 +756,8 @@ MPPI_HD R group_rollout(const G& g, const GroupLink<R>& L, const CostM<R>& C, co
     const R dt = C.dt;
     GroupCostW<R> W;
     group_cost_w(C, W);
+    GroupPairs<R> gp;
+    if (COLL) group_pairs(C, j, gp);
     R du = R(0), S = R(0);
     for (int t = 0; t < T; ++t) {
         const R z = group_normal<R>(seed, tick, k, (uint32_t)t, j);
@@ -743,7 +772,11 @@ MPPI_HD R group_rollout(const G& g, const GroupLink<R>& L, const CostM<R>& C, co
             // registers across the cost part
             R p[3], Q[9];
             qdd = group_dynamics<R, FORCE, G, COLL, true>(g, L, C, grav, ext, q, qd, v + te, v, g.shm, nullptr, p, Q);
-            S += group_cost<R, FORCE, COLL, G, COLL, true>(g, L, C, W, tg, grav, g.shm, nullptr, q, qd, v, p, Q);
+            S += group_cost<R, FORCE, G, COLL, true>(g, L, C, W, tg, grav, g.shm, nullptr, q, qd, v, p, Q);
+            if (COLL) {
+                g.sync();   // the other lanes' handoff
+                S += C.w_coll * group_hits<0, 1>(gp, C, g.shm);
+            }
         } else {
             S += group_step<R, FORCE, G, COLL>(g, L, C, tg, grav, ext, q, qd, v + te, v, qdd);
         }

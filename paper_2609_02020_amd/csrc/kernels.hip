@@ -448,8 +448,12 @@ __device__ __forceinline__ void group_dynamics_loop(const ModelM<R>& M, const Co
     W.wall_c = Cg.wall_c;
     W.force_mode = Cg.force_mode;
     const DevGroup<R> g{j, X};
+    GroupPairs<R> gp;
+    if (COLL) group_pairs(Cg, j, gp);
+    R hits = R(0);
     __syncthreads();
     for (int s = 0; s < T; ++s) {
+        if (COLL && s > 0) hits += group_hits<1, 2>(gp, C, X + ((s - 1) & 1) * kGxPart);
         const R v = torque(s) * L.live;
         R p[3], Q[9];
         const R qdd = group_dynamics<R, FORCE, DevGroup<R>, COLL, true>(
@@ -458,13 +462,20 @@ __device__ __forceinline__ void group_dynamics_loop(const ModelM<R>& M, const Co
         q += qd * dt;
         __syncthreads();
     }
-    *tS = group_terminal(g, L, C, tgs, q, qd);   // lane 7: q = qd = 0
+    R share = group_terminal(g, L, C, tgs, q, qd);   // lane 7: q = qd = 0
+    if (COLL) share += C.w_coll * (hits + group_hits<1, 2>(gp, C, X + ((T - 1) & 1) * kGxPart));
+    *tS = share;
     __syncthreads();
 }
 // Cost: draws the perturbation of step s + 1 (draw(s + 1), s + 1 < T) and
 // evaluates step s - 1 from the pair area; returns this lane's share of the
 // running cost.  One lane of the caller's workgroup (keeps != 0) leaves the
 // target in tgs for the dynamics waves.
+//
+// The collision pairs' rounds alternate between the two waves (the first on
+// the cost wave, which is the shorter); the dynamics wave counts those of
+// step s - 1 from the area that the cost wave reads.  Each lane adds
+// w_coll times its whole count once.
 template <typename R, bool FORCE, bool COLL, typename D>
 __device__ __forceinline__ R group_cost_loop(const ModelM<R>& M, const CostM<R>& Cg, const CostM<R>& C, int j,
                                              const double* target, int T, R* X, D draw, TargetM<R>& tgs, bool keeps)
@@ -476,9 +487,11 @@ __device__ __forceinline__ R group_cost_loop(const ModelM<R>& M, const CostM<R>&
     group_cost_w(Cg, W);
     TargetM<R> tg;
     make_target(target, tg);
+    GroupPairs<R> gp;
+    if (COLL) group_pairs(Cg, j, gp);
     if (keeps) tgs = tg;
     draw(0, L);
-    R Sl = R(0);
+    R Sl = R(0), hits = R(0);
     __syncthreads();
     for (int s = 0; s <= T; ++s) {
         if (s + 1 < T) draw(s + 1, L);
@@ -491,12 +504,13 @@ __device__ __forceinline__ R group_cost_loop(const ModelM<R>& M, const CostM<R>&
             for (int a = 0; a < 3; ++a) pe[a] = h[a];
 #pragma unroll
             for (int a = 0; a < 9; ++a) Re[a] = h[3 + a];
-            Sl += group_cost<R, FORCE, COLL, DevGroup<R>, COLL, true>(g, L, C, W, tg, grav, Xs, nullptr, h[3], h[4], h[5],
-                                                                      pe, Re);
+            if (COLL) hits += group_hits<0, 2>(gp, C, Xs);
+            Sl += group_cost<R, FORCE, DevGroup<R>, COLL, true>(g, L, C, W, tg, grav, Xs, nullptr, h[3], h[4], h[5], pe,
+                                                                Re);
         }
         __syncthreads();
     }
-    return Sl;
+    return COLL ? Sl + C.w_coll * hits : Sl;
 }
 
 template <typename R, typename A, bool FORCE, bool COLL>
@@ -1500,8 +1514,8 @@ static hipError_t update_group_t(const UpdateArgs& a, hipStream_t s)
     const size_t rows = (size_t)a.T * NJ, tile = rows * kGroupTile * sizeof(R);
     // FP32 keeps the workgroup's noise in LDS where it fits.  In FP64 two
     // workgroups share a CU's LDS only without that tile, and the second wave
-    // per SIMD is worth more (K = 16384, T = 36: 363 us against 530 with the
-    // tile): the noise goes through the global buffer (the caller's or the
+    // per SIMD is worth more (K = 16384, T = 36, when this was chosen: 363 us
+    // against 530 with the tile): the noise goes through the global buffer (the caller's or the
     // solver's own), or is regenerated where there is none.
     const int lds_noise = sizeof(R) == 4 && a.merge && tile <= (size_t)kMaxDynLds;
     if (sizeof(R) == 4 && a.merge && !a.want_noise) noise = nullptr;
@@ -1520,13 +1534,14 @@ template <bool EXPLICIT, bool COLL>
 static hipError_t update_dispatch(int precision, bool acc64, bool force, const UpdateArgs& a, hipStream_t s)
 {
     // FP64 takes the lane groups too, except where one lane per sample fills
-    // the chip evenly: between the size at which its flat time (one wave per
-    // SIMD) is reached, and the 768 waves that its LDS lets the chip hold at
-    // once (contact task, T = 18 / 36, lane groups against one lane per
-    // sample: K = 4096 78 / 142 us against 396 / 778, 32768 409 / 753 against
-    // 450 / 878, 40960 492 / 907 against 466 / 910, 65536 750 / 1419 against
-    // 901 / 1782).
-    const bool lanes64 = precision == MPPI_FP64 && a.K > 36864 && a.K <= 49152;
+    // the chip evenly: the top of the range over which its time is flat (one
+    // wave per SIMD), up to the 768 waves that its LDS lets the chip hold at
+    // once.  Contact task, T = 18 / 36, us on lane groups against one lane
+    // per sample: K = 4096 66 / 126 against 396 / 778, 32768 382 / 682
+    // against 449 / 875, 40960 443 / 811 against 463 / 908, 43008 488 / 869
+    // against 481 / 940, 47104 521 / 945 against 491 / 959, 49152 522 / 958
+    // against 484 / 940, 57344 594 / 1109 against 882 / 1731.
+    const bool lanes64 = precision == MPPI_FP64 && a.K > 40960 && a.K <= 49152;
     if (!EXPLICIT && a.waves_per_group == 8 && !lanes64) {
         if (precision == MPPI_FP64)
             return force ? update_group_t<double, double, true, COLL>(a, s)

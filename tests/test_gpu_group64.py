@@ -67,3 +67,17 @@ def test_group64_noise_source_does_not_matter(workloads, K, T):
     for x in (b, c):
         assert torch.equal(a["U_new"], x["U_new"]) and torch.equal(a["costs"], x["costs"])
     solver.close()
+
+
+@pytest.mark.parametrize("K", [40960, 40961, 49152, 49153])
+def test_group64_launch_rule(workloads, K):
+    """Both sides of the sizes at which the default launch changes: costs
+    1e-9 relative against the one-lane launch."""
+    case = resized(workloads["wall_k4096"][2], K, 1)
+    solver = B.Solver(case["robot"], case["cost"], B.FP64)
+    out = device_update(solver, case, case["seed"], 3, B.FP64)
+    solver.set_launch(1)
+    lane = device_update(solver, case, case["seed"], 3, B.FP64)
+    solver.close()
+    assert (np.abs(out["costs"] - lane["costs"]) / np.abs(lane["costs"])).max() <= 1e-9
+    assert np.abs(out["U_new"] - lane["U_new"]).max() <= 1e-9

@@ -785,10 +785,11 @@ struct BatchProblem {
     long long part_off;   // into the partials buffer, in doubles
 };
 
-// The end of a tile on one wave: its Eq. 4 partial (noise regenerated), and
-// the merge of its problem's partials by the wave whose tile completes the
-// problem.  tr: LDS scratch [64][kLdsRowPad], wl [64].
-__device__ __forceinline__ void batch_tile_done(const BatchProblem& Pb, int2 it, float s, int lane,
+// The end of a tile on one wave: its Eq. 4 partial (from the du tile of the
+// rollout in LDS, or with noise regenerated where tile is null: the same
+// sums), and the merge of its problem's partials by the wave whose tile
+// completes the problem.  tr: LDS scratch [64][kLdsRowPad], wl [64].
+__device__ __forceinline__ void batch_tile_done(const BatchProblem& Pb, int2 it, float s, int lane, const float* tile,
                                                 const CostM<float>& C, uint64_t seed, uint32_t tick, uint32_t k,
                                                 float* tr, double* wl, double* parts, unsigned int* counters,
                                                 const double* U_nom, double* U_new, double* U_shift, int* status)
@@ -797,9 +798,9 @@ __device__ __forceinline__ void batch_tile_done(const BatchProblem& Pb, int2 it,
     double* pbase = parts + Pb.part_off;
     wave_sync();
     if (Pb.acc64)
-        wave_partial<float, double>(s, lane, T, Pb.lambda, nullptr, C, seed, tick, k, tr, wl, pbase + (size_t)it.y * P);
+        wave_partial<float, double>(s, lane, T, Pb.lambda, tile, C, seed, tick, k, tr, wl, pbase + (size_t)it.y * P);
     else
-        wave_partial<float, float>(s, lane, T, Pb.lambda, nullptr, C, seed, tick, k, tr, reinterpret_cast<float*>(wl),
+        wave_partial<float, float>(s, lane, T, Pb.lambda, tile, C, seed, tick, k, tr, reinterpret_cast<float*>(wl),
                                    reinterpret_cast<float*>(pbase) + (size_t)it.y * P);
     __threadfence();
     const unsigned done_tiles =
@@ -890,7 +891,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(COLL ? 1
                 if (costs) costs[Pb.k_off + k] = s;
             }
         }
-        batch_tile_done(Pb, it, s, lane, C, seed, tick, (uint32_t)k, tr[wid], wl[wid], parts, counters, U_nom, U_new,
+        batch_tile_done(Pb, it, s, lane, nullptr, C, seed, tick, (uint32_t)k, tr[wid], wl[wid], parts, counters, U_nom, U_new,
                         U_shift, status);
     }
     // the last wave out resets the queue for the next launch
@@ -911,7 +912,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(COLL ? 1
 // Tiles, partials, counters and the queue as in batch_kernel, at workgroup
 // granularity.  T = 18, against batch_kernel with a wave per tile: 8 tiles 130
 // us (191), 200 tiles 137 (199), 256 tiles 145 (206); past one tile per CU some
-// CU would run two in turn, 1.4 times batch_kernel's time.
+// CU would run two in turn, 1.4 times batch_kernel's time.  The CU's LDS
+// has room for the tile's noise up to kSplitTileRows rows (T <= 27): drawing
+// it a second time for the partial took 6.6 us of a
+// 50-problem tick of 204 (K = 256, T = 18).
+constexpr int kSplitTileRows = kMaxDynLds / (kLdsRowPad * 4);   // 189
 template <bool COLL>
 __global__ __launch_bounds__(128) void batch_split_kernel(
     const BatchProblem* __restrict__ probs, const ModelM<float>* __restrict__ models,
@@ -923,7 +928,7 @@ __global__ __launch_bounds__(128) void batch_split_kernel(
 {
     __shared__ SplitShared sh;
     __shared__ float Us[kMaxTBatch * NJ];
-    __shared__ float tr[64 * kLdsRowPad];
+    __shared__ float tr[kSplitTileRows * kLdsRowPad];   // the du tile [7T][kLdsRowPad], or wave_partial's scratch
     __shared__ double wl[64];
     __shared__ int sItem;
     __shared__ CostM<float> Csh;
@@ -947,21 +952,23 @@ __global__ __launch_bounds__(128) void batch_split_kernel(
         const double* q0 = q + it.x * NJ;
         const double* qd0 = qd + it.x * NJ;
         const double* tgt = target + (size_t)it.x * 13;
+        float* tile = T * NJ <= kSplitTileRows ? tr : nullptr;
+        float* tk = tile ? tile + lane : nullptr;
         float s;
         if (COLL && Pb.coll)
-            s = Pb.force ? split_rollout<true, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, nullptr, sh,
-                                                     lane, wave)
-                         : split_rollout<false, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, nullptr,
-                                                      sh, lane, wave);
+            s = Pb.force ? split_rollout<true, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh, lane,
+                                                     wave)
+                         : split_rollout<false, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
+                                                      lane, wave);
         else
-            s = Pb.force ? split_rollout<true, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, nullptr,
-                                                      sh, lane, wave)
-                         : split_rollout<false, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, nullptr,
-                                                       sh, lane, wave);
+            s = Pb.force ? split_rollout<true, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
+                                                      lane, wave)
+                         : split_rollout<false, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
+                                                       lane, wave);
         if (wave == 1) {
             if (costs && k < K) costs[Pb.k_off + k] = s;
-            batch_tile_done(Pb, it, s, lane, Csh, seed, tick, (uint32_t)k, tr, wl, parts, counters, U_nom, U_new, U_shift,
-                            status);
+            batch_tile_done(Pb, it, s, lane, tile, Csh, seed, tick, (uint32_t)k, tr, wl, parts, counters, U_nom, U_new,
+                            U_shift, status);
         }
         __syncthreads();
     }

@@ -37,6 +37,8 @@ def make_io(batch, cases, torch, dev):
     ([1], 1, False, {}),
     ([63, 64, 65, 129], 18, False, {"lambda": 0.01}),
     ([100, 1000, 300], 64, True, {"dt": 0.002}),
+    ([100, 65], 27, True, {"dt": 0.002}),
+    ([100, 65], 28, False, {"dt": 0.002, "noise_rho": 0.5}),
     ([4096, 4096, 4096, 4096], 10, False, {"lambda": 100.0}),
     ([4096, 4096, 4096, 4097], 10, False, {"lambda": 100.0}),
     ([500, 70], 12, False, {"iterations": 3, "noise_rho": 0.5, "lambda": 100.0}),

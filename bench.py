@@ -55,16 +55,16 @@ FP32_PEAK_TFLOPS = 157.3          # MI355X vector FP32 (AMD published)
 # known size (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000 on gfx950), taken on the
 # kernel sources whose digest is recorded here; reported as null once the
 # sources differ.
-PROFILED_DIGEST = "9389df91679e6d76"
-PROFILED_TRAFFIC = {"update_group_kernel": 340034 + 159744 + 476486 + 1956,   # K=4096, T=18 contact workload:
+PROFILED_DIGEST = "09c26eaa00518006"
+PROFILED_TRAFFIC = {"update_group_kernel": 323502 + 159744 + 476529 + 1956,   # K=4096, T=18 contact workload:
                                                             # the group kernel and its merge launch
                     # 64-problem batch, per launch shape the autotuner may pick (waves per
                     # group x groups); the one-lane shapes mostly register-spill stores
-                    "batch_kernel_w1x2048": 106361459 + 324806144,
-                    "batch_kernel_w2x1024": 118716882 + 352157440,
-                    "batch_kernel_w4x512": 104396139 + 333902592,
-                    "batch_kernel_w8x256": 5992043 + 10652006,    # eight lanes per sample
-                    "mlp_train": 5863884 + 1737728 + 4833908 + 678432}   # forward/backward + weight
+                    "batch_kernel_w1x2048": 38669824 + 292384963,
+                    "batch_kernel_w2x1024": 42508063 + 302536499,
+                    "batch_kernel_w4x512": 42360054 + 308100700,
+                    "batch_kernel_w8x256": 6431867 + 15497155,    # eight lanes per sample
+                    "mlp_train": 5821440 + 1737728 + 4814725 + 678431}   # forward/backward + weight
                                                                           # gradients, 512 rows
 
 

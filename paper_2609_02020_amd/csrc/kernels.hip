@@ -337,7 +337,13 @@ __global__ __launch_bounds__(128) void update_split_kernel(
 // convention) from the du tile in LDS (or from regenerated noise when the
 // tile does not fit); group_merge_kernel, launched next, merges them.  Every
 // group runs through the rollout (samples past K too, storing nothing), so
-// the DPP moves always see a converged wave.
+// the DPP moves always see a converged wave.  Bound by the dynamics wave's
+// chain of T dependent steps, which issues an instruction every 4.4 - 4.6
+// cycles at one wave per SIMD; contact task, K = 4096, T = 18, this kernel
+// and the merge together: 39.1 us (41.9 with the force estimate's pivot
+// columns broadcast, the link forces formed about the origin and the motion
+// subspaces read late); FP64, K = 16384, T = 36: 327 us on two waves per
+// SIMD (833 on one lane per sample).
 constexpr int kGroupPairs = 2;
 constexpr int kGroupSamples = 8 * kGroupPairs;
 constexpr int kGroupThreads = 128 * kGroupPairs;
@@ -649,7 +655,8 @@ __global__ __launch_bounds__(kGroupThreads, sizeof(R) == 8 ? 2 : 1) void update_
     // the partials are merged by group_merge_kernel, launched next on the
     // same stream: the kernel boundary orders them, with no per-workgroup
     // fence (an agent-scope release writes back the XCD's L2, and hundreds
-    // of them cost more than the merge)
+    // of them cost more than the merge; with 32 partials or fewer a merge
+    // here is slower too: K = 256 33.9 -> 35.2 us)
 }
 
 // Eq. 4 from the np workgroup partials of update_group_kernel ((m, s) pairs
@@ -914,8 +921,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(COLL ? 1
 // us (191), 200 tiles 137 (199), 256 tiles 145 (206); past one tile per CU some
 // CU would run two in turn, 1.4 times batch_kernel's time.  The CU's LDS
 // has room for the tile's noise up to kSplitTileRows rows (T <= 27): drawing
-// it a second time for the partial took 6.6 us of a
-// 50-problem tick of 204 (K = 256, T = 18).
+// it a second time for the partial took 6.6 us of a 50-problem tick of 204
+// (K = 256, T = 18).
 constexpr int kSplitTileRows = kMaxDynLds / (kLdsRowPad * 4);   // 189
 template <bool COLL>
 __global__ __launch_bounds__(128) void batch_split_kernel(

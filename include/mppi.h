@@ -152,7 +152,9 @@ typedef struct mppi_solver* mppi_handle_t;
 
 /* Creates a solver.  Copies both structs (the caller may free them);
  * validates them; allocates device buffers for (K, T): noise K*T*7 and
- * costs K in the rollout precision, plus small staging buffers.
+ * costs K in the rollout precision, plus small staging buffers, and in FP64
+ * (articulated-body route) K*T*7 of scratch for the updates, which do
+ * without it where it does not fit.
  * Errors: MPPI_EINVAL (null, n_joints != 7, K or T out of range, dt <= 0,
  * lambda <= 0, sigma < 0, mass <= 0, inertia not PD or violating the
  * triangle inequality, non-finite field, unknown mode), MPPI_ENOMEM,
@@ -267,7 +269,8 @@ int mppi_update_noalloc(const mppi_robot_params* robot, const mppi_cost_params* 
 
 /* Stage entry points (the two halves of mppi_update_async, same io):
  * rollout only writes costs and noise; weights reads them (Eq. 4) and
- * writes U_new, U_shift and status. */
+ * writes U_new, U_shift and status.  Only a rollout writes the internal
+ * noise buffer (io->noise NULL); updates of the handle leave it alone. */
 int mppi_rollout_async(mppi_handle_t h, const mppi_device_io* io, void* stream);
 int mppi_weights_async(mppi_handle_t h, const mppi_device_io* io, void* stream);
 

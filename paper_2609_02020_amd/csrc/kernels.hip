@@ -1529,10 +1529,11 @@ static hipError_t update_group_t(const UpdateArgs& a, hipStream_t s)
     // FP32 keeps the workgroup's noise in LDS where it fits.  In FP64 two
     // workgroups share a CU's LDS only without that tile, and the second wave
     // per SIMD is worth more (K = 16384, T = 36, when this was chosen: 363 us
-    // against 530 with the tile): the noise goes through the global buffer (the caller's or the
-    // solver's own), or is regenerated where there is none.
+    // against 530 with the tile): the noise goes through a global buffer (the
+    // caller's, or scratch of the fused update alone), or is regenerated where
+    // there is none (K = 16384, T = 36 387 us against 327).
     const int lds_noise = sizeof(R) == 4 && a.merge && tile <= (size_t)kMaxDynLds;
-    if (sizeof(R) == 4 && a.merge && !a.want_noise) noise = nullptr;
+    if (a.merge && !a.want_noise) noise = sizeof(R) == 8 ? (R*)a.du : nullptr;
     hipLaunchKernelGGL((update_group_kernel<R, A, FORCE, COLL>), grid, dim3(kGroupThreads),
                        rows * sizeof(R) + (lds_noise ? tile : 0), s, (const ModelM<R>*)a.model,
                        (const CostM<R>*)a.cost, a.q0, a.qd0, a.target, a.U_nom, a.seed, (uint32_t)a.tick, a.K, a.T,

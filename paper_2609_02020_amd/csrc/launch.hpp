@@ -34,6 +34,7 @@ struct UpdateArgs {
     void* costs;            // R [K]
     int merge;              // 0: rollouts only
     int want_noise;         // the caller asked for the noise (global copy)
+    void* du;               // FP64: scratch for the noise of a fused update (R [T][7][K]) or null
     void* parts;            // A [ceil(K/64)][2 + 7T]
     unsigned int* counter;  // zero before the launch; the kernel leaves it zero
     double* U_new;

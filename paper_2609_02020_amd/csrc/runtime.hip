@@ -31,6 +31,7 @@ struct mppi_solver {
     CostM<float>* d_cf = nullptr;
     CostM<double>* d_cd = nullptr;
     void* d_noise = nullptr;     // R [T][7][K]
+    void* d_du = nullptr;        // FP64: R [T][7][K] of a fused update's own (null: drawn again)
     void* d_costs = nullptr;     // R [K]
     void* d_parts = nullptr;     // per-wave Eq. 4 partials (FP64-sized)
     unsigned int* d_counter = nullptr;  // last-block counter of the fused one-/two-wave updates
@@ -185,6 +186,7 @@ void release(mppi_solver* h)
     (void)hipFree(h->d_cf);
     (void)hipFree(h->d_cd);
     (void)hipFree(h->d_noise);
+    (void)hipFree(h->d_du);
     (void)hipFree(h->d_costs);
     (void)hipFree(h->d_parts);
     (void)hipFree(h->d_counter);
@@ -218,6 +220,7 @@ int update_enqueue_one(mppi_solver* h, const mppi_device_io* io, hipStream_t s, 
     a.T = h->cost.T;
     a.lambda = h->cost.lambda;
     a.noise = noise;
+    a.du = h->d_du;
     a.costs = costs;
     a.merge = merge ? 1 : 0;
     a.parts = h->d_parts;
@@ -471,6 +474,13 @@ int mppi_create(const mppi_robot_params* robot, const mppi_cost_params* cost, mp
               hipHostMalloc(&h->h_costs, K * rs, hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc(&h->h_status, sizeof(int), hipHostMallocDefault) == hipSuccess;
     if (!ok) { release(h); return MPPI_ENOMEM; }
+    // an FP64 update writes its noise here and not to d_noise, which holds a
+    // rollout's for the weights; without the memory it draws the noise twice
+    if (cost->precision == MPPI_FP64 && cost->dynamics == MPPI_DYN_ABA &&
+        hipMalloc(&h->d_du, K * T * MPPI_NJ * rs) != hipSuccess) {
+        h->d_du = nullptr;
+        (void)hipGetLastError();
+    }
     if (hipStreamCreateWithFlags(&h->stream, hipStreamNonBlocking) != hipSuccess) { release(h); return MPPI_EDEVICE; }
     if (hipMemset(h->d_counter, 0, sizeof(unsigned int)) != hipSuccess ||
         hipMemcpy(h->d_raw, robot, sizeof *robot, hipMemcpyHostToDevice) != hipSuccess ||

@@ -1545,19 +1545,38 @@ static hipError_t update_group_t(const UpdateArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// FP64 with no shape chosen: one lane per sample where that is faster than
+// the lane groups.  Either kernel takes whole rounds of what the chip holds:
+// the groups 8192 samples a round (two workgroups of 16 per CU), one lane
+// per sample one wave per SIMD, 65536 samples, or with the update's noise
+// tile in LDS 49152 at T = 7 .. 10 (three workgroups per CU; two at
+// T = 11 .. 13, and from T = 14 on the noise is drawn twice).  The lanes take
+// it where one of their rounds costs less than the group rounds it replaces:
+// 5 of them, 6 without the force estimate, where the lanes write the caller's
+// noise or at T > 8, fewer at T <= 2.  Contact task, us on groups / lanes: updates
+// T = 1, K = 32768 72 / 62; T = 4, K = 32768 120 / 129, 49152 174 / 150, 81920
+// 283 / 311; T = 8, K = 49152 268 / 232, 65536 353 / 421; T = 10, K = 40960
+// 266 / 281, 49152 317 / 297; T = 11, K = 49152 347 / 544; T = 18, K = 49152
+// 497 / 492, 393216 3886 / 3828 (the only range where the groups are behind,
+// by up to 1.5 %).  Rollouts alone, T = 18: K = 49152 452 / 446, 65536 596 / 515,
+// 81920 734 / 896.  Collision pairs: the groups throughout (T = 18, K = 49152
+// 586 / 1410).
+static bool lanes64(bool force, const UpdateArgs& a)
+{
+    const bool own = force && !(a.merge && a.want_noise);
+    if (a.collision || (a.merge && a.T > (own ? 10 : 6))) return false;
+    const int resident = 256 * 64 * (a.merge && a.T > 6 ? 3 : 4);   // samples
+    const int rounds = (a.K + resident - 1) / resident, group_rounds = (a.K + 8191) / 8192;
+    const int worth = a.T <= 2 ? a.T + 2 : (own && a.T <= 8 ? 5 : 6);
+    return group_rounds >= worth * rounds;
+}
+
 template <bool EXPLICIT, bool COLL>
 static hipError_t update_dispatch(int precision, bool acc64, bool force, const UpdateArgs& a, hipStream_t s)
 {
-    // FP64 takes the lane groups too, except where one lane per sample fills
-    // the chip evenly: the top of the range over which its time is flat (one
-    // wave per SIMD), up to the 768 waves that its LDS lets the chip hold at
-    // once.  Contact task, T = 18 / 36, us on lane groups against one lane
-    // per sample: K = 4096 66 / 126 against 396 / 778, 32768 382 / 682
-    // against 449 / 875, 40960 443 / 811 against 463 / 908, 43008 488 / 869
-    // against 481 / 940, 47104 521 / 945 against 491 / 959, 49152 522 / 958
-    // against 484 / 940, 57344 594 / 1109 against 882 / 1731.
-    const bool lanes64 = precision == MPPI_FP64 && a.K > 40960 && a.K <= 49152;
-    if (!EXPLICIT && a.waves_per_group == 8 && !lanes64) {
+    const int shape = a.waves_per_group ? a.waves_per_group
+                                        : (precision == MPPI_FP64 && !EXPLICIT && lanes64(force, a) ? 1 : 8);
+    if (!EXPLICIT && shape == 8) {
         if (precision == MPPI_FP64)
             return force ? update_group_t<double, double, true, COLL>(a, s)
                          : update_group_t<double, double, false, COLL>(a, s);
@@ -1566,12 +1585,12 @@ static hipError_t update_dispatch(int precision, bool acc64, bool force, const U
                          : update_group_t<float, double, false, COLL>(a, s);
         return force ? update_group_t<float, float, true, COLL>(a, s) : update_group_t<float, float, false, COLL>(a, s);
     }
-    if (a.waves_per_group == 8) {   // the two-wave launch where groups do not apply
+    if (shape == 8) {   // the two-wave launch where groups do not apply
         UpdateArgs b = a;
         b.waves_per_group = 2;
         return update_dispatch<EXPLICIT, COLL>(precision, acc64, force, b, s);
     }
-    if (!EXPLICIT && a.waves_per_group == 2 && precision == MPPI_FP32) {
+    if (!EXPLICIT && shape == 2 && precision == MPPI_FP32) {
         if (force) return acc64 ? update_split_t<double, true, COLL>(a, s) : update_split_t<float, true, COLL>(a, s);
         return acc64 ? update_split_t<double, false, COLL>(a, s) : update_split_t<float, false, COLL>(a, s);
     }

@@ -44,7 +44,8 @@ struct UpdateArgs {
     int collision;          // the collision term is on (n_pairs > 0)
     int waves_per_group;    // 2: the two-wave split update (FP32 articulated-body
                             // rollouts); 8: eight lanes per sample (articulated-body
-                            // rollouts; otherwise as 2); else 1
+                            // rollouts; otherwise as 2); 1; 0: 8, or 1 where that
+                            // is faster in FP64
 };
 
 // One fused launch: rollouts, per-wave Eq. 4 partials, last-block merge.

@@ -347,8 +347,9 @@ int mppi_batch_update_async(mppi_batch_t b, const mppi_batch_io* io, uint64_t ti
 
 /* Launch shape: waves per workgroup and workgroup count.  1, 2 or 4: one
  * lane per sample, every wave takes 64-sample tiles from the work list (the
- * articulated-body rollouts; with 2 in a batch of at most 256 tiles the two
- * waves take one tile together, as mppi_set_launch(h, 2) does); 8: eight lanes per sample, a workgroup of
+ * articulated-body rollouts; with 2, in a batch of at most 256 tiles and
+ * with a workgroup for each, the two waves take one tile together, as
+ * mppi_set_launch(h, 2) does); 8: eight lanes per sample, a workgroup of
  * eight waves takes a 64-sample tile together (eight samples per wave, the
  * eight-lane arithmetic of mppi_set_launch(h, 8) with each step's dynamics
  * and cost on one wave).  Both write the same partials of Eq. 4, so they

@@ -914,10 +914,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(COLL ? 1
 // The batched update with two waves per tile (split_rollout: the arithmetic
 // of batch_kernel per sample, the dynamics of a step beside the noise, force
 // estimate and cost of its neighbours), for batches of at most
-// kBatchSplitTiles tiles, one workgroup of two waves per CU: there batch_kernel
+// kBatchSplitTiles tiles, one workgroup of two waves per tile: there batch_kernel
 // has at most one wave per CU and its time is one tile's chain of steps.
-// Tiles, partials, counters and the queue as in batch_kernel, at workgroup
-// granularity.  T = 18, against batch_kernel with a wave per tile: 8 tiles 130
+// Tiles, partials and counters as in batch_kernel.  T = 18, against batch_kernel with a wave per tile: 8 tiles 130
 // us (191), 200 tiles 137 (199), 256 tiles 145 (206); past one tile per CU some
 // CU would run two in turn, 1.4 times batch_kernel's time.  The CU's LDS
 // has room for the tile's noise up to kSplitTileRows rows (T <= 27): drawing
@@ -927,7 +926,7 @@ constexpr int kSplitTileRows = kMaxDynLds / (kLdsRowPad * 4);   // 189
 template <bool COLL>
 __global__ __launch_bounds__(128) void batch_split_kernel(
     const BatchProblem* __restrict__ probs, const ModelM<float>* __restrict__ models,
-    const int2* __restrict__ items, int nitems, unsigned int* queue, unsigned int* done, unsigned int* counters,
+    const int2* __restrict__ items, unsigned int* counters,
     const double* __restrict__ q, const double* __restrict__ qd, const double* __restrict__ target,
     const double* U_nom, double* U_new, double* U_shift, float* __restrict__ costs, int* __restrict__ status,
     const uint64_t* __restrict__ seeds, const uint64_t* __restrict__ tickp, int iter, int niter,
@@ -937,57 +936,39 @@ __global__ __launch_bounds__(128) void batch_split_kernel(
     __shared__ float Us[kMaxTBatch * NJ];
     __shared__ float tr[kSplitTileRows * kLdsRowPad];   // the du tile [7T][kLdsRowPad], or wave_partial's scratch
     __shared__ double wl[64];
-    __shared__ int sItem;
     __shared__ CostM<float> Csh;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t tick = (uint32_t)(*tickp * (uint64_t)niter + (uint64_t)iter);
-    for (;;) {
-        if (tid == 0) sItem = (int)atomicAdd(queue, 1u);
-        __syncthreads();
-        const int item = __builtin_amdgcn_readfirstlane(sItem);
-        if (item >= nitems) break;
-        const int2 it = items[item];
-        const BatchProblem& Pb = probs[it.x];
-        const int T = Pb.T, K = Pb.K;
-        if (wave == 0) wave_copy(&Csh, Pb.cost, lane);
-        for (int i = tid; i < T * NJ; i += 128) Us[i] = float(U_nom[Pb.u_off + i]);
-        // problem p's model through the restrict-qualified argument at a
-        // uniform index (scalar loads), as in batch_kernel
-        const ModelM<float>& M = models[it.x];
-        const int k = it.y * 64 + lane;
-        const uint64_t seed = seeds[it.x];
-        const double* q0 = q + it.x * NJ;
-        const double* qd0 = qd + it.x * NJ;
-        const double* tgt = target + (size_t)it.x * 13;
-        float* tile = T * NJ <= kSplitTileRows ? tr : nullptr;
-        float* tk = tile ? tile + lane : nullptr;
-        float s;
-        if (COLL && Pb.coll)
-            s = Pb.force ? split_rollout<true, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh, lane,
-                                                     wave)
-                         : split_rollout<false, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
-                                                      lane, wave);
-        else
-            s = Pb.force ? split_rollout<true, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
-                                                      lane, wave)
-                         : split_rollout<false, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
-                                                       lane, wave);
-        if (wave == 1) {
-            if (costs && k < K) costs[Pb.k_off + k] = s;
-            batch_tile_done(Pb, it, s, lane, tile, Csh, seed, tick, (uint32_t)k, tr, wl, parts, counters, U_nom, U_new,
-                            U_shift, status);
-        }
-        __syncthreads();
-    }
-    // the last workgroup out resets the queue for the next launch
-    if (tid == 0) {
-        __threadfence();
-        const unsigned out = atomicAdd(done, 1u);
-        if (out == gridDim.x - 1) {
-            *queue = 0u;
-            *done = 0u;
-            __threadfence();
-        }
+    const int2 it = items[blockIdx.x];
+    const BatchProblem& Pb = probs[it.x];
+    const int T = Pb.T, K = Pb.K;
+    if (wave == 0) wave_copy(&Csh, Pb.cost, lane);
+    for (int i = tid; i < T * NJ; i += 128) Us[i] = float(U_nom[Pb.u_off + i]);
+    // problem p's model through the restrict-qualified argument at a
+    // uniform index (scalar loads), as in batch_kernel
+    const ModelM<float>& M = models[it.x];
+    const int k = it.y * 64 + lane;
+    const uint64_t seed = seeds[it.x];
+    const double* q0 = q + it.x * NJ;
+    const double* qd0 = qd + it.x * NJ;
+    const double* tgt = target + (size_t)it.x * 13;
+    float* tile = T * NJ <= kSplitTileRows ? tr : nullptr;
+    float* tk = tile ? tile + lane : nullptr;
+    float s;
+    if (COLL && Pb.coll)
+        s = Pb.force ? split_rollout<true, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh, lane,
+                                                 wave)
+                     : split_rollout<false, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
+                                                  lane, wave);
+    else
+        s = Pb.force ? split_rollout<true, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
+                                                  lane, wave)
+                     : split_rollout<false, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
+                                                   lane, wave);
+    if (wave == 1) {
+        if (costs && k < K) costs[Pb.k_off + k] = s;
+        batch_tile_done(Pb, it, s, lane, tile, Csh, seed, tick, (uint32_t)k, tr, wl, parts, counters, U_nom, U_new,
+                        U_shift, status);
     }
 }
 
@@ -1644,12 +1625,11 @@ template <int W, bool COLL> static hipError_t batch_t(const BatchArgs& a, int gr
     return hipGetLastError();
 }
 
-template <bool COLL> static hipError_t batch_split_t(const BatchArgs& a, int groups, hipStream_t s)
+template <bool COLL> static hipError_t batch_split_t(const BatchArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL((batch_split_kernel<COLL>), dim3(groups < a.nitems ? groups : a.nitems), dim3(128), 0, s,
-                       (const BatchProblem*)a.probs, (const ModelM<float>*)a.models, (const int2*)a.items, a.nitems,
-                       a.queue, a.done, a.counters, a.q, a.qd, a.target, a.U_nom, a.U_new, a.U_shift, a.costs,
-                       a.status, a.seeds, a.tick, a.iter, a.niter, a.parts);
+    hipLaunchKernelGGL((batch_split_kernel<COLL>), dim3(a.nitems), dim3(128), 0, s, (const BatchProblem*)a.probs,
+                       (const ModelM<float>*)a.models, (const int2*)a.items, a.counters, a.q, a.qd, a.target, a.U_nom,
+                       a.U_new, a.U_shift, a.costs, a.status, a.seeds, a.tick, a.iter, a.niter, a.parts);
     return hipGetLastError();
 }
 
@@ -1669,7 +1649,11 @@ hipError_t launch_batch(const BatchArgs& a, int waves_per_group, int groups, hip
     case 8: return a.collision ? batch_group_t<true>(a, groups, s) : batch_group_t<false>(a, groups, s);
     case 1: return a.collision ? batch_t<1, true>(a, groups, s) : batch_t<1, false>(a, groups, s);
     case 2:
-        if (a.nitems <= kBatchSplitTiles) return a.collision ? batch_split_t<true>(a, groups, s) : batch_split_t<false>(a, groups, s);
+        // the two waves on one tile, if every tile has a workgroup; with fewer
+        // a wave takes a tile alone, as twice as many are then in flight (200
+        // tiles on 100 workgroups: 200 us, 242 with two waves per tile)
+        if (a.nitems <= kBatchSplitTiles && groups >= a.nitems)
+            return a.collision ? batch_split_t<true>(a, s) : batch_split_t<false>(a, s);
         return a.collision ? batch_t<2, true>(a, groups, s) : batch_t<2, false>(a, groups, s);
     case 4: return a.collision ? batch_t<4, true>(a, groups, s) : batch_t<4, false>(a, groups, s);
     default: return hipErrorInvalidValue;

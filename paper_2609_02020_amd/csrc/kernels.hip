@@ -179,7 +179,7 @@ struct SplitShared {
 template <bool FORCE, bool COLL>
 __device__ __forceinline__ float split_rollout(const ModelM<float>& Mc, const CostM<float>& Cc, const double* q0,
                                                const double* qd0, const double* target, const float* Us, int T, int K,
-                                               int k, uint64_t seed, uint32_t tick, float* noise_k, float* tile_k,
+                                               int k, uint64_t seed, uint32_t tick, float* noise_k, int noise_stride, float* tile_k,
                                                SplitShared& sh, int lane, int wave)
 {
     __syncthreads();
@@ -200,7 +200,7 @@ __device__ __forceinline__ float split_rollout(const ModelM<float>& Mc, const Co
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             sh.nb[0][j * 64 + lane] = du[j];
-            if (noise_k) noise_k[(size_t)j * K] = du[j];
+            if (noise_k) noise_k[(size_t)j * noise_stride] = du[j];
             if (tile_k) tile_k[j * kLdsRowPad] = du[j];
         }
     }
@@ -246,7 +246,7 @@ __device__ __forceinline__ float split_rollout(const ModelM<float>& Mc, const Co
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     sh.nb[(s + 1) & 1][j * 64 + lane] = du[j];
-                    if (noise_k) noise_k[(size_t)((s + 1) * NJ + j) * K] = du[j];
+                    if (noise_k) noise_k[(size_t)((s + 1) * NJ + j) * noise_stride] = du[j];
                     if (tile_k) tile_k[((s + 1) * NJ + j) * kLdsRowPad] = du[j];
                 }
             }
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(128) void update_split_kernel(
     const int k = blockIdx.x * 64 + lane;
     float* tile = reinterpret_cast<float*>(dyn_lds);   // [rows][65] (noise) or [64][65] (regeneration)
     const float s_lane = split_rollout<FORCE, COLL>(*Mp, Csh, q0, qd0, target, Us, T, K, k, seed, tick,
-                                                    (noise && k < K) ? noise + k : nullptr,
+                                                    (noise && k < K) ? noise + k : nullptr, K,
                                                     lds_noise ? tile + lane : nullptr, sh, lane, wave);
     if (wave == 1 && k < K) S[k] = s_lane;
     if (!merge) return;
@@ -916,13 +916,17 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(COLL ? 1
 // estimate and cost of its neighbours), for batches of at most
 // kBatchSplitTiles tiles, one workgroup of two waves per tile: there batch_kernel
 // has at most one wave per CU and its time is one tile's chain of steps.
-// Tiles, partials and counters as in batch_kernel.  T = 18, against batch_kernel with a wave per tile: 8 tiles 130
-// us (191), 200 tiles 137 (199), 256 tiles 145 (206); past one tile per CU some
-// CU would run two in turn, 1.4 times batch_kernel's time.  The CU's LDS
-// has room for the tile's noise up to kSplitTileRows rows (T <= 27): drawing
-// it a second time for the partial took 6.6 us of a 50-problem tick of 204
-// (K = 256, T = 18).
-constexpr int kSplitTileRows = kMaxDynLds / (kLdsRowPad * 4);   // 189
+// Tiles, partials and counters as in batch_kernel.  The dynamics wave's chain
+// bounds it: T = 18, against batch_kernel with a wave per tile: 200 tiles 126
+// us (229), 256 tiles 133 (236); past one tile per CU some CU would run two in
+// turn.  LDS holds little beyond the double-buffered handoff (72 KB), so that
+// the tiles of a second batch on another stream fit on the same CUs: two
+// batches of 256 tiles at T = 40 take 295 us together, one 283 (493 on
+// batch_kernel; 550 with a noise tile in LDS as well, 121 KB).  The noise
+// therefore goes through global memory (du, up to du_rows rows) and comes
+// into the handoff's place at the end; past that, or without the buffer, the
+// partial draws it again (6.6 us more at T = 18).
+static_assert(kBatchSplitRows * kLdsRowPad <= 2 * kHandoff * 64 && 64 * kLdsRowPad <= 2 * kHandoff * 64, "the tile");
 template <bool COLL>
 __global__ __launch_bounds__(128) void batch_split_kernel(
     const BatchProblem* __restrict__ probs, const ModelM<float>* __restrict__ models,
@@ -930,11 +934,10 @@ __global__ __launch_bounds__(128) void batch_split_kernel(
     const double* __restrict__ q, const double* __restrict__ qd, const double* __restrict__ target,
     const double* U_nom, double* U_new, double* U_shift, float* __restrict__ costs, int* __restrict__ status,
     const uint64_t* __restrict__ seeds, const uint64_t* __restrict__ tickp, int iter, int niter,
-    double* __restrict__ parts)
+    double* __restrict__ parts, float* du, int du_rows)
 {
     __shared__ SplitShared sh;
     __shared__ float Us[kMaxTBatch * NJ];
-    __shared__ float tr[kSplitTileRows * kLdsRowPad];   // the du tile [7T][kLdsRowPad], or wave_partial's scratch
     __shared__ double wl[64];
     __shared__ CostM<float> Csh;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -952,22 +955,29 @@ __global__ __launch_bounds__(128) void batch_split_kernel(
     const double* q0 = q + it.x * NJ;
     const double* qd0 = qd + it.x * NJ;
     const double* tgt = target + (size_t)it.x * 13;
-    float* tile = T * NJ <= kSplitTileRows ? tr : nullptr;
-    float* tk = tile ? tile + lane : nullptr;
+    float* own = du && T * NJ <= du_rows ? du + (size_t)blockIdx.x * du_rows * 64 + lane : nullptr;
     float s;
     if (COLL && Pb.coll)
-        s = Pb.force ? split_rollout<true, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh, lane,
+        s = Pb.force ? split_rollout<true, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, own, 64, nullptr, sh, lane,
                                                  wave)
-                     : split_rollout<false, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
+                     : split_rollout<false, true>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, own, 64, nullptr, sh,
                                                   lane, wave);
     else
-        s = Pb.force ? split_rollout<true, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
+        s = Pb.force ? split_rollout<true, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, own, 64, nullptr, sh,
                                                   lane, wave)
-                     : split_rollout<false, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, nullptr, tk, sh,
+                     : split_rollout<false, false>(M, Csh, q0, qd0, tgt, Us, T, K, k, seed, tick, own, 64, nullptr, sh,
                                                    lane, wave);
+    // the handoff is no longer read: while wave 1 evaluates the terminal cost,
+    // wave 0 moves the tile's noise there
+    float* tr = sh.hb[0];
+    if (wave == 0 && own) {
+#pragma unroll 18
+        for (int r = 0; r < T * NJ; ++r) tr[r * kLdsRowPad + lane] = own[(size_t)r * 64];
+    }
+    __syncthreads();
     if (wave == 1) {
         if (costs && k < K) costs[Pb.k_off + k] = s;
-        batch_tile_done(Pb, it, s, lane, tile, Csh, seed, tick, (uint32_t)k, tr, wl, parts, counters, U_nom, U_new,
+        batch_tile_done(Pb, it, s, lane, own ? tr : nullptr, Csh, seed, tick, (uint32_t)k, tr, wl, parts, counters, U_nom, U_new,
                         U_shift, status);
     }
 }
@@ -1629,7 +1639,7 @@ template <bool COLL> static hipError_t batch_split_t(const BatchArgs& a, hipStre
 {
     hipLaunchKernelGGL((batch_split_kernel<COLL>), dim3(a.nitems), dim3(128), 0, s, (const BatchProblem*)a.probs,
                        (const ModelM<float>*)a.models, (const int2*)a.items, a.counters, a.q, a.qd, a.target, a.U_nom,
-                       a.U_new, a.U_shift, a.costs, a.status, a.seeds, a.tick, a.iter, a.niter, a.parts);
+                       a.U_new, a.U_shift, a.costs, a.status, a.seeds, a.tick, a.iter, a.niter, a.parts, a.du, a.du_rows);
     return hipGetLastError();
 }
 

@@ -71,6 +71,8 @@ struct BatchArgs {
     const uint64_t* seeds;  // [n]
     const uint64_t* tick;   // [1] (device)
     double* parts;          // partials, sized by the host
+    float* du;              // two waves per tile: noise [nitems][du_rows][64], or null
+    int du_rows;
     int collision;          // some problem has the collision term
     int iter, niter;        // iteration iter of niter: Philox tick word = *tick * niter + iter
 };
@@ -113,6 +115,7 @@ constexpr int kWeightsBlock = 256;
 constexpr int kWeightsRows = 2;
 constexpr int kMaxT = 256;
 constexpr int kMaxTBatch = 64;   // horizon limit of the batched kernel
-constexpr int kBatchSplitTiles = 256;   // batches up to this many tiles: two waves per tile
+constexpr int kBatchSplitTiles = 256;   // batches up to this many tiles: two waves per tile,
+constexpr int kBatchSplitRows = 245;    // which keep their noise up to 7 T of this
 
 }  // namespace mppi

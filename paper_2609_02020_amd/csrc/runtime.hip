@@ -780,6 +780,8 @@ struct mppi_batch {
     int nitems = 0;
     unsigned int* d_sync = nullptr;   // queue, done, counters[n]
     double* d_parts = nullptr;
+    float* d_du = nullptr;        // batches of few tiles: their noise [nitems][du_rows][64] (null: drawn again)
+    int du_rows = 0;
     uint64_t* d_tick = nullptr;   // [0]: graph replays (advanced by the graph), [1]: eager launches
     int wpg = 1, groups = 1024;
     int collision = 0;            // some problem has the collision term
@@ -805,6 +807,7 @@ void batch_release(mppi_batch* b)
     (void)hipFree(b->d_items);
     (void)hipFree(b->d_sync);
     (void)hipFree(b->d_parts);
+    (void)hipFree(b->d_du);
     (void)hipFree(b->d_iter);
     (void)hipFree(b->d_tick);
     delete b;
@@ -831,6 +834,8 @@ BatchArgs batch_args(mppi_batch* b, const mppi_batch_io* io, const uint64_t* tic
     a.seeds = io->seed;
     a.tick = tick_slot;
     a.parts = b->d_parts;
+    a.du = b->d_du;
+    a.du_rows = b->du_rows;
     a.collision = b->collision;
     a.iter = 0;
     a.niter = 1;
@@ -946,6 +951,13 @@ int mppi_batch_create(const mppi_problem_desc* descs, int n, mppi_batch_t* out)
               hipMalloc(&b->d_iter, sizeof(double) * 2 * b->u_total) == hipSuccess &&
               hipMalloc(&b->d_tick, 2 * sizeof(uint64_t)) == hipSuccess;
     if (!ok) { batch_release(b); return MPPI_ENOMEM; }
+    for (int p = 0; p < n; ++p)
+        b->du_rows = std::max(b->du_rows, std::min(b->cost[p].T * MPPI_NJ, kBatchSplitRows));
+    if (b->nitems <= kBatchSplitTiles &&
+        hipMalloc(&b->d_du, sizeof(float) * 64 * b->du_rows * b->nitems) != hipSuccess) {
+        b->d_du = nullptr;
+        (void)hipGetLastError();
+    }
     std::vector<CostM<float>> cf(n);
     std::vector<CostM<double>> cd(n);
     std::vector<char> probs(batch_problem_bytes() * n);

@@ -1,0 +1,62 @@
+"""Two waves per tile keep their noise in global memory up to 35 steps (and
+draw it again above): both sides of that line and batches of mixed horizons
+equal the one-wave-per-tile launch (1e-6 relative, as between all launches
+of the per-lane arithmetic).  Two such batches on two streams share the CUs:
+the same bits as one after the other, in well under twice one's time."""
+import time
+
+import numpy as np
+import pytest
+
+from paper_2609_02020_amd import binding as B
+from gpu_util import torch_dev
+from test_gpu_batch_split import make_io, problems
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("horizons", [(35,), (36,), (1, 64), (18, 35, 36, 64)])
+def test_noise_through_memory(workloads, horizons):
+    torch, dev = torch_dev()
+    cases = [c for T in horizons for c in problems(workloads, [65, 200], T, **{"dt": 0.002, "lambda": 100.0})]
+    batch = B.Batch([(c["robot"], c["cost"]) for c in cases])
+    two, one = make_io(batch, cases, torch, dev), make_io(batch, cases, torch, dev)
+    batch.update_async(two, tick=4)
+    batch.set_launch(1, 300)
+    batch.update_async(one, tick=4)
+    torch.cuda.synchronize()
+    assert ((two["costs"] - one["costs"]).double().abs() / one["costs"].double().abs()).max() <= 1e-6
+    assert (two["U_new"] - one["U_new"]).abs().max() <= 1e-4
+    batch.close()
+
+
+def test_two_batches_share_the_cus(workloads):
+    torch, dev = torch_dev()
+    cases = problems(workloads, [1024] * 16, 40, dt=0.002)
+    batches = [B.Batch([(c["robot"], c["cost"]) for c in cases]) for _ in range(2)]
+    ios = [make_io(b, cases, torch, dev) for b in batches]
+    ios[1]["seed"] += 100
+    streams = [torch.cuda.Stream() for _ in batches]
+    torch.cuda.synchronize()
+
+    def seconds(n, steps=30):
+        best = float("inf")
+        for _ in range(5):
+            t0 = time.perf_counter()
+            for i in range(steps):
+                for b, io, s in list(zip(batches, ios, streams))[:n]:
+                    b.update_async(io, tick=i, stream=s)
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - t0) / steps)
+        return best
+    alone = seconds(1)
+    both = seconds(2)
+    together = [io["U_new"].clone() for io in ios]
+    for b, io, want in zip(batches, ios, together):
+        io["U_new"].fill_(float("nan"))
+        b.update_async(io, tick=29)
+        torch.cuda.synchronize()
+        assert torch.equal(io["U_new"], want)
+        b.close()
+    print("two batches of 256 tiles: one alone %.1f us, both %.1f us" % (alone * 1e6, both * 1e6))
+    assert both <= 1.5 * alone

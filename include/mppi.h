@@ -235,7 +235,7 @@ int mppi_update_async(mppi_handle_t h, const mppi_device_io* io, void* stream);
  * returns it in *best_launch (may be NULL) and the mean update times in
  * times_ms[3] (launch 8, 2, 1; may be NULL).  With an autotune cache the
  * choice is stored under (architecture, K, T, precision, dynamics route,
- * cost terms, iterations) and reused without timing (times_ms set to -1).
+ * cost terms, iterations, version of the kernels) and reused without timing (times_ms set to -1).
  * Errors: MPPI_EINVAL (null, budget_ms < 1), MPPI_EDEVICE. */
 int mppi_autotune(mppi_handle_t h, const mppi_device_io* io, int budget_ms, void* stream,
                   int* best_launch, float* times_ms);
@@ -366,8 +366,9 @@ int mppi_batch_set_launch(mppi_batch_t b, int waves_per_group, int groups);
  * order.  The io buffers are written by the timing runs.  With an autotune
  * cache (mppi_set_autotune_cache) the choice is stored under a key of the
  * device architecture, the batch's total sample-steps (power-of-two
- * bucket), its horizon range, the precision, the union of its cost terms
- * and the iteration count; a later call with the same key takes the stored
+ * bucket), its horizon range, the precision, the union of its cost terms,
+ * the iteration count, whether it has at most 256 tiles and the version of
+ * the kernels; a later call with the same key takes the stored
  * shape without timing and sets every times_ms entry to -1. */
 int mppi_batch_autotune(mppi_batch_t b, const mppi_batch_io* io, int reps, void* stream,
                         int* best_waves_per_group, int* best_groups, float* times_ms);

@@ -290,9 +290,13 @@ int check_io(const mppi_solver* h, const mppi_device_io* io, bool need_out)
 // ---------------------------------------------------------------------------
 // autotune cache: a JSON object in a file, one entry per line,
 //   "<key>": {"waves_per_group": w, "groups": g, "ms": t},
-// keyed by the device architecture, the problem sizes, the precision and
-// the cost terms; read and rewritten whole (write to a temporary, rename)
+// keyed by the device architecture, the problem sizes, the precision, the
+// cost terms and kTuneKernels; read and rewritten whole (write to a
+// temporary, rename)
 // ---------------------------------------------------------------------------
+// Raised with any change of the kernels that a launch shape runs: a choice
+// timed on other kernels is timed again.
+constexpr int kTuneKernels = 2;
 struct TuneEntry {
     int wpg = 0, groups = 0;
     double ms = 0;
@@ -535,9 +539,9 @@ int mppi_autotune(mppi_handle_t h, const mppi_device_io* io, int budget_ms, void
     if (budget_ms < 1) return MPPI_EINVAL;
     const int shapes[3] = {8, 2, 1};
     char key[256];
-    std::snprintf(key, sizeof key, "solver|%s|K%d|T%d|%s|dyn%d|mask%02x|it%d", arch_name().c_str(), h->cost.K,
+    std::snprintf(key, sizeof key, "solver|%s|K%d|T%d|%s|dyn%d|mask%02x|it%d|k%d", arch_name().c_str(), h->cost.K,
                   h->cost.T, h->cost.precision == MPPI_FP64 ? "fp64" : "fp32", h->cost.dynamics, cost_mask(h->cost),
-                  iterations_of(h->cost));
+                  iterations_of(h->cost), kTuneKernels);
     TuneEntry e;
     if (tune_lookup(key, &e) && (e.wpg == 1 || e.wpg == 2 || e.wpg == 8)) {
         h->waves_per_group = e.wpg;
@@ -1072,7 +1076,9 @@ int mppi_batch_autotune(mppi_batch_t b, const mppi_batch_io* io, int reps, void*
     const int wpgs[4] = {1, 2, 4, 8};
     const int waves[4] = {256, 512, 1024, 2048};
     // cache key: architecture, total sample-steps (power-of-two bucket),
-    // horizon range, precision, union of the problems' cost terms, iterations
+    // horizon range, precision, union of the problems' cost terms, iterations,
+    // and on which side of kBatchSplitTiles its shapes' kernels are
+    const bool few = b->nitems <= kBatchSplitTiles;
     long long kt = 0;
     int tmin = 1 << 30, tmax = 0;
     unsigned mask = 0;
@@ -1085,8 +1091,8 @@ int mppi_batch_autotune(mppi_batch_t b, const mppi_batch_io* io, int reps, void*
     int lg = 0;
     while ((2LL << lg) <= kt) ++lg;
     char key[256];
-    std::snprintf(key, sizeof key, "batch|%s|kt2^%d|T%d-%d|fp32|mask%02x|it%d", arch_name().c_str(), lg, tmin, tmax,
-                  mask, b->iterations);
+    std::snprintf(key, sizeof key, "batch|%s|kt2^%d|T%d-%d|fp32|mask%02x|it%d|%s|k%d", arch_name().c_str(), lg, tmin,
+                  tmax, mask, b->iterations, few ? "few" : "many", kTuneKernels);
     TuneEntry e;
     if (tune_lookup(key, &e) && (e.wpg == 1 || e.wpg == 2 || e.wpg == 4 || e.wpg == 8) && e.groups >= 1 &&
         e.groups <= (1 << 16)) {
@@ -1101,12 +1107,21 @@ int mppi_batch_autotune(mppi_batch_t b, const mppi_batch_io* io, int reps, void*
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return MPPI_EDEVICE;
     BatchArgs a = batch_args(b, io, b->d_tick + 1);
-    float best = 1e30f;
+    float best = 1e30f, split_ms = 0;
     int bw = b->wpg, bg = b->groups, idx = 0;
     st = MPPI_OK;
     for (int wi = 0; wi < 4 && !st; ++wi)
         for (int vi = 0; vi < 4 && !st; ++vi, ++idx) {
             const int w = wpgs[wi], g = waves[vi] / w;
+            // two waves per tile are one launch whatever the workgroup count:
+            // timed once, and kept with the largest, so that it stays that
+            // for every batch of this key
+            const bool split = w == 2 && few && g >= b->nitems;
+            if (split && split_ms > 0) {
+                if (times_ms) times_ms[idx] = split_ms;
+                if (split_ms == best) bg = g;
+                continue;
+            }
             // one untimed launch, then `reps` timed ones
             if (launch_set_tick(b->d_tick + 1, 0, s) != hipSuccess || launch_batch(a, w, g, s) != hipSuccess ||
                 hipEventRecord(e0, s) != hipSuccess) { st = MPPI_EDEVICE; break; }
@@ -1118,6 +1133,7 @@ int mppi_batch_autotune(mppi_batch_t b, const mppi_batch_io* io, int reps, void*
                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess) { st = MPPI_EDEVICE; break; }
             ms /= reps;
             if (times_ms) times_ms[idx] = ms;
+            if (split) split_ms = ms;
             if (ms < best) { best = ms; bw = w; bg = g; }
         }
     (void)hipEventDestroy(e0);

@@ -39,7 +39,7 @@ METRIC = "MPPI update rate (Hz) + ABA rollout steps/s, K=4096 T=18 7-DoF, FP32"
 # quantities by the composite-rigid-body route and executes more
 # instructions for them (every lane factorises M).  Contact workload
 # (force estimate, wall, orientation cost on).
-FLOPS_PER_SAMPLE_STEP = 6475
+FLOPS_PER_SAMPLE_STEP = 6472
 FLOPS_PER_SAMPLE_TERMINAL = 822
 # Free-space problems (no wall, no force term, no orientation cost).
 FLOPS_PER_SAMPLE_STEP_FREE = 4573

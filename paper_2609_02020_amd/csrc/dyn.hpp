@@ -588,8 +588,7 @@ MPPI_HD void force_estimate(const ForceIn<R>& fi, const R* v, const R* g, int fo
     F[3] = x[0] - rf[0]; F[4] = x[1] - rf[1]; F[5] = x[2] - rf[2];
 }
 
-// ext: EXTW_NONE, EXTW_CONST (world wrench F_ext at the EE point, current
-// configuration) or EXTW_WALL (the cost's wall model).  tau: joint torques
+// ext: EXTW_WALL (the cost's wall model) or EXTW_NONE.  tau: joint torques
 // (sampled torque plus any joint-space external torque).  v: sampled torque
 // for the force estimate (FORCE only).
 // hand (FORCE only): when non-null, the inputs of the force estimate are
@@ -664,25 +663,19 @@ MPPI_HD void dyn_step(const ModelM<R>& M, const CostM<R>& Cst, int ext, const R*
     out.pee[0] = pw[0] + ree_w[0]; out.pee[1] = pw[1] + ree_w[1]; out.pee[2] = pw[2] + ree_w[2];
 #pragma unroll
     for (int i = 0; i < 9; ++i) out.Rn[i] = Rw[i];
-    // external wrench on the last link: world force F at the EE point and
-    // world moment N, about p_n: (N + ree_w x F, F)
-    if (ext != EXTW_NONE) {
-        R Fw[3] = {R(0), R(0), R(0)}, Nw[3] = {R(0), R(0), R(0)};
-        if (ext == EXTW_WALL) {
-            R wxr[3];
-            cross3(vw, ree_w, wxr);
-            const R vee[3] = {vw[3] + wxr[0], vw[4] + wxr[1], vw[5] + wxr[2]};
-            R delta = Cst.wall_d0 - dot3(Cst.wall_n, out.pee);
-            R ddelta = -dot3(Cst.wall_n, vee);
-            R mag = hinge(Cst.wall_k * delta + Cst.wall_c * ddelta);
-            Fw[0] = Cst.wall_n[0] * mag; Fw[1] = Cst.wall_n[1] * mag; Fw[2] = Cst.wall_n[2] * mag;
-        } else {
-            Fw[0] = Cst.F_ext[0]; Fw[1] = Cst.F_ext[1]; Fw[2] = Cst.F_ext[2];
-            Nw[0] = Cst.F_ext[3]; Nw[1] = Cst.F_ext[4]; Nw[2] = Cst.F_ext[5];
-        }
+    // the wall's force F on the last link at the EE point, about p_n:
+    // (ree_w x F, F)
+    if (ext == EXTW_WALL) {
+        R wxr[3];
+        cross3(vw, ree_w, wxr);
+        const R vee[3] = {vw[3] + wxr[0], vw[4] + wxr[1], vw[5] + wxr[2]};
+        R delta = Cst.wall_d0 - dot3(Cst.wall_n, out.pee);
+        R ddelta = -dot3(Cst.wall_n, vee);
+        R mag = hinge(Cst.wall_k * delta + Cst.wall_c * ddelta);
+        const R Fw[3] = {Cst.wall_n[0] * mag, Cst.wall_n[1] * mag, Cst.wall_n[2] * mag};
         R rf[3];
         cross3(ree_w, Fw, rf);
-        pA[NJ - 1][0] -= Nw[0] + rf[0]; pA[NJ - 1][1] -= Nw[1] + rf[1]; pA[NJ - 1][2] -= Nw[2] + rf[2];
+        pA[NJ - 1][0] -= rf[0]; pA[NJ - 1][1] -= rf[1]; pA[NJ - 1][2] -= rf[2];
         pA[NJ - 1][3] -= Fw[0]; pA[NJ - 1][4] -= Fw[1]; pA[NJ - 1][5] -= Fw[2];
     }
 

@@ -167,23 +167,16 @@ __device__ __forceinline__ void store_transposed(const uint16_t* tile, int ncols
     }
 }
 
-// One lane's N result rows of column col (batch rows row0 + 0..N-1, row0 a
-// multiple of N) into the transposed global buffer [feature][Bp] in operand
-// order: the rows are contiguous there, so one store per lane.
-template <int N>
-__device__ __forceinline__ void store_frag_T(uint16_t* dstT, int Bp, int row0, int col, const uint16_t (&o)[N])
+// One lane's four result rows of column col (batch rows row0 + 0..3, row0 a
+// multiple of 4; training has 16 rows per workgroup) into the transposed
+// global buffer [feature][Bp] in operand order: the rows are contiguous
+// there, so one store per lane.
+__device__ __forceinline__ void store_frag_T(uint16_t* dstT, int Bp, int row0, int col, const uint16_t (&o)[4])
 {
-    uint16_t* d = dstT + frag_index(col, row0, Bp);
-    if constexpr (N == 4) {
-        uint2 v;
-        v.x = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
-        v.y = (uint32_t)o[2] | ((uint32_t)o[3] << 16);
-        *reinterpret_cast<uint2*>(d) = v;
-    } else if constexpr (N == 2) {
-        *reinterpret_cast<uint32_t*>(d) = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
-    } else {
-        *d = o[0];
-    }
+    uint2 v;
+    v.x = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
+    v.y = (uint32_t)o[2] | ((uint32_t)o[3] << 16);
+    *reinterpret_cast<uint2*>(dstT + frag_index(col, row0, Bp)) = v;
 }
 
 // this wave's bias values of a hidden layer (columns nb + 16 j + lane mod 16)
@@ -224,7 +217,9 @@ __device__ __forceinline__ void hidden_forward(const uint16_t* A, const BFrag<K,
             if (e < rows) o[e] = row0 + e < rows ? to_bf16(gelu_f(zz)) : (uint16_t)0;
             out[(row0 + e) * kLda + col] = o[e];
         }
-        if (dstT) store_frag_T<NE>(dstT, Bp, b0 + row0, col, o);
+        if constexpr (R == kMlpWgRows) {
+            if (dstT) store_frag_T(dstT, Bp, b0 + row0, col, o);
+        }
     }
 }
 
@@ -251,7 +246,7 @@ __device__ __forceinline__ void hidden_backward(const uint16_t* E, const BFrag<K
             o[e] = to_bf16(acc[j][e] * gelu_d(zv[j][e]));
             if (out) out[(row0 + e) * kLda + col] = o[e];
         }
-        store_frag_T<NE>(dstT, Bp, b0 + row0, col, o);
+        store_frag_T(dstT, Bp, b0 + row0, col, o);
     }
 }
 
@@ -394,7 +389,7 @@ __global__ __launch_bounds__(kThreads) void mlp_forward_kernel(MlpDev d, const f
                         buf[0][row * kLda + col] = o[e];
                     }
                 }
-                if (TRAIN) store_frag_T<NE>(d.eT4, d.Bp, b0 + row0, col, o);
+                if constexpr (TRAIN) store_frag_T(d.eT4, d.Bp, b0 + row0, col, o);
             }
         }
         if (!TRAIN) return;
@@ -411,15 +406,17 @@ __global__ __launch_bounds__(kThreads) void mlp_forward_kernel(MlpDev d, const f
         d.lossp[blockIdx.x] = sl;
     }
 
-    BFrag<kMlpHid, kHidCT> g3;
-    load_frag(d.W3t, nh, g3, lane);
-    hidden_backward<R, kMlpOutPad>(buf[0], g4, z3, buf[1], w, lane, d.eT3, d.Bp, b0);
-    __syncthreads();
-    BFrag<kMlpHid, kHidCT> g2;
-    load_frag(d.W2t, nh, g2, lane);
-    hidden_backward<R, kMlpHid>(buf[1], g3, z2, buf[0], w, lane, d.eT2, d.Bp, b0);
-    __syncthreads();
-    hidden_backward<R, kMlpHid>(buf[0], g2, z1, nullptr, w, lane, d.eT1, d.Bp, b0);
+    if constexpr (TRAIN) {
+        BFrag<kMlpHid, kHidCT> g3;
+        load_frag(d.W3t, nh, g3, lane);
+        hidden_backward<R, kMlpOutPad>(buf[0], g4, z3, buf[1], w, lane, d.eT3, d.Bp, b0);
+        __syncthreads();
+        BFrag<kMlpHid, kHidCT> g2;
+        load_frag(d.W2t, nh, g2, lane);
+        hidden_backward<R, kMlpHid>(buf[1], g3, z2, buf[0], w, lane, d.eT2, d.Bp, b0);
+        __syncthreads();
+        hidden_backward<R, kMlpHid>(buf[0], g2, z1, nullptr, w, lane, d.eT1, d.Bp, b0);
+    }
 }
 
 // Adam state of one parameter, read before its gradient is known
@@ -643,7 +640,6 @@ __global__ void mlp_features_kernel(MlpDev d, int n, const double* __restrict__ 
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
-
 
 }  // namespace
 

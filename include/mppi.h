@@ -355,7 +355,8 @@ int mppi_batch_update_async(mppi_batch_t b, const mppi_batch_io* io, uint64_t ti
  * and cost on one wave).  Both write the same partials of Eq. 4, so they
  * give the same U_new to FP32 rounding.  Default: 2 and one workgroup per
  * tile up to 256 tiles, else 1 and min(tiles, 2048) workgroups (1024 with
- * the collision term). */
+ * the collision term, or if no horizon is longer than one step, or two in a
+ * batch without force costs). */
 int mppi_batch_set_launch(mppi_batch_t b, int waves_per_group, int groups);
 
 /* Times every launch shape of the built-in search space (waves per

@@ -558,9 +558,9 @@ template <typename R> MPPI_HD void group_pairs(const CostM<R>& C, int j, GroupPa
 // read at a selected address, not in a branch per kind of segment: lanes of
 // one wave hold both kinds (a wave ran the four cases of a pair one after
 // another).  With this and the rounds dealt over both waves of a pair of
-// waves, K = 4096, T = 18 with 20 pairs takes 44.3 us (56.8 with all rounds
-// on the cost wave and the branches; 47.5 with the first and third round on
-// the dynamics wave instead of the second); FP64 79 us (94).
+// waves, K = 4096, T = 18 with 20 pairs takes 46.4 us (59.0 with all rounds
+// on the cost wave and the branches; 7 % longer with the first and third
+// round on the dynamics wave instead of the second); FP64 79 us (94).
 template <int FIRST, int STEP, typename R>
 MPPI_HD R group_hits(const GroupPairs<R>& P, const CostM<R>& C, const R* X)
 {

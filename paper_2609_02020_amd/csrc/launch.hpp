@@ -35,7 +35,7 @@ struct UpdateArgs {
     int merge;              // 0: rollouts only
     int want_noise;         // the caller asked for the noise (global copy)
     void* du;               // FP64: scratch for the noise of a fused update (R [T][7][K]) or null
-    void* parts;            // A [ceil(K/64)][2 + 7T]
+    void* parts;            // A, one partial of 2 + 7T per workgroup (update_parts_bytes)
     unsigned int* counter;  // zero before the launch; the kernel leaves it zero
     double* U_new;
     double* U_shift;

@@ -935,13 +935,23 @@ int mppi_batch_create(const mppi_problem_desc* descs, int n, mppi_batch_t* out)
     // SIMD, with the collision term one) or as there are tiles: the
     // 64-problem batch takes 959 us on 1024 waves, 696 on 2048; 200 tiles take
     // 231 us on 1024 waves, 199 on 200 (a workgroup without a tile still
-    // passes through the queue)
+    // passes through the queue).  Horizons of one step, without a force cost
+    // of up to two, are over before the second wave pays: 4096 tiles at T = 1
+    // 187 us on 1024 waves, 197 on 2048, at T = 2 215 and 228 (with the force
+    // cost 242 and 222)
+    int tmax = 0;
+    bool force = false;
+    for (const auto& c : b->cost) {
+        tmax = std::max(tmax, c.T);
+        force = force || has_force(c);
+    }
+    const bool one_per_simd = b->collision || tmax <= (force ? 1 : 2);
     if (b->nitems <= kBatchSplitTiles) {
         b->wpg = 2;
         b->groups = b->nitems;
     } else {
         b->wpg = 1;
-        b->groups = std::min(b->nitems, b->collision ? 1024 : 2048);
+        b->groups = std::min(b->nitems, one_per_simd ? 1024 : 2048);
     }
     bool ok = hipMalloc(&b->d_raw, sizeof(mppi_robot_params) * n) == hipSuccess &&
               hipMalloc(&b->d_mf, sizeof(ModelM<float>) * n) == hipSuccess &&
@@ -955,8 +965,7 @@ int mppi_batch_create(const mppi_problem_desc* descs, int n, mppi_batch_t* out)
               hipMalloc(&b->d_iter, sizeof(double) * 2 * b->u_total) == hipSuccess &&
               hipMalloc(&b->d_tick, 2 * sizeof(uint64_t)) == hipSuccess;
     if (!ok) { batch_release(b); return MPPI_ENOMEM; }
-    for (int p = 0; p < n; ++p)
-        b->du_rows = std::max(b->du_rows, std::min(b->cost[p].T * MPPI_NJ, kBatchSplitRows));
+    b->du_rows = std::min(tmax * MPPI_NJ, kBatchSplitRows);
     if (b->nitems <= kBatchSplitTiles &&
         hipMalloc(&b->d_du, sizeof(float) * 64 * b->du_rows * b->nitems) != hipSuccess) {
         b->d_du = nullptr;

@@ -234,7 +234,8 @@ template <typename R> struct HostGroup {
         s->barrier();
         return r;
     }
-    // the device's butterfly: x + x^1, then + ^2, then + ^4
+    // a butterfly, x + x^1, then + ^2, then + ^4 (the device sums by rotations
+    // of the row, the joints 4, 2 and 1 on: another order)
     R sum(R x) const
     {
         s->slot[j] = double(x);

@@ -36,15 +36,15 @@ def test_two_batches_share_the_cus(workloads):
     batches = [B.Batch([(c["robot"], c["cost"]) for c in cases]) for _ in range(2)]
     ios = [make_io(b, cases, torch, dev) for b in batches]
     ios[1]["seed"] += 100
-    streams = [torch.cuda.Stream() for _ in batches]
     torch.cuda.synchronize()
 
     def seconds(n, steps=30):
         best = float("inf")
-        for _ in range(5):
+        for _ in range(5):   # other streams each time: two of them may share a hardware queue
+            streams = [torch.cuda.Stream() for _ in range(n)]
             t0 = time.perf_counter()
             for i in range(steps):
-                for b, io, s in list(zip(batches, ios, streams))[:n]:
+                for b, io, s in zip(batches, ios, streams):
                     b.update_async(io, tick=i, stream=s)
             torch.cuda.synchronize()
             best = min(best, (time.perf_counter() - t0) / steps)
